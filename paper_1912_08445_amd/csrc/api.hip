@@ -63,7 +63,10 @@ void dfree(T *&p)
 // hipGetSymbolAddress returned for that device (scratch_ptr).
 constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr size_t kScratchHead = 256;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// The per-point bounds of the far-wing test follow the staging: 8 bytes per point, for as many
+// points as the staging can hold (FP32, one line).
+constexpr size_t kScratchFar = kScratchBytes;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchFar];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -147,6 +150,7 @@ nlte_status ensure_work(nlte_ctx *c)
     const size_t lcbytes = (size_t)P * c->n_lines * sizeof(double2);
     nlte_status st;
     if ((st = dalloc(c, (char **)&c->d_lc, lcbytes))) return st;
+    if ((st = dalloc(c, &c->d_far, (size_t)P))) return st;
     if ((st = dalloc(c, &c->d_pops_a, (size_t)P * c->n_lev))) return st;
     if ((st = dalloc(c, &c->d_pops_b, (size_t)P * c->n_lev))) return st;
     if ((st = dalloc(c, &c->d_J, (size_t)P * c->n_lines))) return st;
@@ -169,9 +173,15 @@ void set_launch_shape(nlte_ctx *c, SolveArgs &a, bool fp32)
     // three waves spill inside the node loops; five FP32 lines fit three waves with a few
     // spills outside them, and the third wave takes the disc's FP32 sweep from 4.0 to 3.5 s)
     a.waves = (c->cfg.waves >= 1 && c->cfg.waves <= 3) ? c->cfg.waves : ((lpl <= 2 || fp32) ? 3 : 2);
-    // long-segment mode (profile recurrence, far-wing collapse) where sub-step segments are
-    // long: more than two elimination steps per cached cell on average
-    a.collapse = c->cfg.long_seg >= 0 ? c->cfg.long_seg : (c->total_steps > 2 * c->total_cells ? 1 : 0);
+    // long-segment mode (the profile by recurrence within a segment) where sub-step segments
+    // are long on average and a lane holds at most three lines.  Measured short / long on an
+    // outflow of 20,011 points, two lines per lane, against its elimination steps per cell:
+    // FP64 6.08 / 6.24 ms at 3.1, 6.40 / 5.53 at 5.0, 6.63 / 4.79 at 13; FP32 3.72 / 3.78 at
+    // 1.6, 3.89 / 3.46 at 3.1.  Five lines per lane: the recurrence's state spills in FP64
+    // (the disc of 30,011 points at 2.2: 95 / 155 ms; an outflow with nine lines at 16.6:
+    // 6.1 / 7.5) and gains nothing in FP32 (4.38 / 4.35 there, the disc 50.9 / 52.1).
+    const double per_cell = c->total_cells > 0 ? (double)c->total_steps / (double)c->total_cells : 0.0;
+    a.collapse = c->cfg.long_seg >= 0 ? c->cfg.long_seg : (lpl <= 3 && per_cell > (fp32 ? 2.0 : 3.5) ? 1 : 0);
     // the most staged nodes whose LDS keeps the register budget's occupancy (160 KiB per CU):
     // dynamic and static bytes in the units the hardware allocates (counted without them, the
     // disc's FP32 form took 48 nodes and lost one wave per CU to the rounding: 3.40 s per
@@ -194,6 +204,7 @@ SolveArgs solve_args(nlte_ctx *c, double *J, double *Jeff, double *L)
     SolveArgs a{};
     a.cell = c->d_cell;
     a.lc = c->d_lc;
+    a.far = c->d_far;
     a.roff = c->d_roff;
     a.rcells = c->d_rcells;
     a.dir = c->d_dir;
@@ -252,6 +263,7 @@ void drop_graphs(nlte_ctx *c)
 // then nothing is timed, counted or allocated.
 struct FsScratch {
     void *lc;
+    float2 *far;
     unsigned long long *counter;
 };
 
@@ -262,11 +274,13 @@ nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, do
     const int fp32 = c->params.precision == NLTE_PREC_FP32_BULK;
     void *lcbuf = sc ? sc->lc : c->d_lc;
     int64_t *maser = sc ? nullptr : c->d_maser;
-    auto lc = [&] { return launch_line_coef(c->sp, c->d_cell, d_pops, c->P, fp32, lcbuf, maser, s); };
+    float2 *far = sc ? sc->far : c->d_far;
+    auto lc = [&] { return launch_line_coef(c->sp, c->d_cell, d_pops, c->P, fp32, lcbuf, maser, c->d_ibdy, far, s); };
     HIPCHK(c, capture ? lc() : timed(c, c->st_line_coef, s, lc));
     SolveArgs a = solve_args(c, d_J, d_Jeff, d_L);
     if (sc) {
         a.lc = sc->lc;
+        a.far = sc->far;
         a.work_counter = sc->counter;
         a.exec_steps = nullptr;
     }
@@ -576,7 +590,7 @@ nlte_status ensure_band(nlte_ctx *c)
 nlte_status formal_solve_band_impl(nlte_ctx *c, const double *d_pops, double *d_J, double *d_Jeff, double *d_L,
                                    hipStream_t s, bool ali)
 {
-    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, s));
+    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, c->d_ibdy, c->d_far, s));
     SolveArgs a = solve_args(c, d_J, d_Jeff, d_L);
     if (a.lines_per_wave / a.ngrp > 2) {   // the band kernel takes one or two lines per lane
         a.lines_per_wave = a.ngrp * 2;
@@ -764,7 +778,7 @@ nlte_status need_scat(nlte_ctx *c)
 nlte_status formal_solve_scat_impl(nlte_ctx *c, const double *d_pops, const double *d_jin, double *d_J,
                                    double *d_Jeff, double *d_L, double *d_jout, hipStream_t s, bool ali)
 {
-    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, s));
+    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, nullptr, nullptr, s));
     ScatArgs a{};
     a.cell = c->d_cell;
     a.lc = c->d_lc;
@@ -917,6 +931,7 @@ void nlte_destroy(nlte_ctx *c)
     dfree(c->d_roff);
     dfree(c->d_rcells);
     dfree(c->d_lc);
+    dfree(c->d_far);
     dfree(c->d_pops_a);
     dfree(c->d_pops_b);
     dfree(c->d_J);
@@ -1552,7 +1567,8 @@ nlte_status nlte_formal_solve_noalloc_dev(nlte_ctx *c, const double *d_pops, dou
                         std::to_string(kScratchBytes - kScratchHead) + " (use nlte_formal_solve_dev)");
     (void)hipSetDevice(c->device);
     hipStream_t s = pick(c, stream);
-    FsScratch sc{static_cast<unsigned char *>(base) + kScratchHead, static_cast<unsigned long long *>(base)};
+    unsigned char *b8 = static_cast<unsigned char *>(base);
+    FsScratch sc{b8 + kScratchHead, reinterpret_cast<float2 *>(b8 + kScratchBytes), static_cast<unsigned long long *>(base)};
     // enqueue only: no event timing (which would synchronise), no step counting
     return formal_solve_impl(c, d_pops, d_J, d_Jeff, d_L, s, false, true, &sc);
 }
@@ -2425,7 +2441,7 @@ nlte_status nlte_image_dev(nlte_ctx *c, const double *d_pops, int ray, int line,
     }
     HIPCHK(c, hipMemcpyAsync(c->d_vch, v_ch, sizeof(double) * n_ch, hipMemcpyHostToDevice, s));
     // FP64 line coefficients of these populations
-    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, s));
+    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, nullptr, nullptr, s));
     const double nu = c->nu[line];
     ImageArgs a{};
     a.cell = c->d_cell;

@@ -34,46 +34,73 @@ namespace nlte {
 //   k_eta = (h nu/4 pi) n_u A_ul,  k_chi = (h nu/4 pi)(n_l B_lu - n_u B_ul),
 // line-centre opacity kappa = k_chi / (sqrt(pi) dnu), dnu = nu v_w / c, S = k_eta / k_chi.
 // Non-positive opacity (population inversion) is clamped to kappa = S = 0 and counted.
+// One thread per (point, line), a block on whole points.  far (nullable): per point, powers of
+// two above the largest kappa and the largest S / I_bdy (at least 1) of its lines, as
+// exponents: the formal solve's far-wing test reads these 8 bytes per cell instead of every
+// line's coefficients.
 template <bool F32>
-__global__ void k_line_coef(SpeciesDev sp, const CellRec *__restrict__ cell,
-                            const double *__restrict__ pops, int64_t P, void *__restrict__ lc,
-                            unsigned long long *__restrict__ maser)
+__global__ __launch_bounds__(256) void k_line_coef(SpeciesDev sp, const CellRec *__restrict__ cell,
+                                                   const double *__restrict__ pops, int64_t P,
+                                                   void *__restrict__ lc, unsigned long long *__restrict__ maser,
+                                                   const double *__restrict__ ibdy, float2 *__restrict__ far)
 {
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= P * sp.n_lines) return;
-    int64_t p = q / sp.n_lines;
-    int l = (int)(q - p * sp.n_lines);
-    const double *n = pops + p * sp.n_lev;
-    double nu_ = sp.nu[l];
-    double pre = sp.pre[l];
-    double nup = n[sp.lu[l]], nlo = n[sp.ll[l]];
-    double keta = pre * nup * sp.A[l];
-    double kchi = pre * (nlo * sp.Blu[l] - nup * sp.Bul[l]);
-    double kap = 0.0, S = 0.0;
-    if (kchi > 0.0) {
-        double dnu = nu_ * cell[p].vw / kC;
-        kap = kchi / (kSqrtPi * dnu);
-        S = keta / kchi;
-    } else if (maser) {
-        atomicAdd(maser, 1ull);
+    __shared__ float2 s_far[256];
+    const int nl = sp.n_lines, per_block = 256 / nl;
+    const int lp = threadIdx.x / nl, l = threadIdx.x - lp * nl;
+    const int64_t p = blockIdx.x * (int64_t)per_block + lp;
+    const bool on = lp < per_block && p < P;
+    if (on) {
+        const double *n = pops + p * sp.n_lev;
+        double nu_ = sp.nu[l];
+        double pre = sp.pre[l];
+        double nup = n[sp.lu[l]], nlo = n[sp.ll[l]];
+        double keta = pre * nup * sp.A[l];
+        double kchi = pre * (nlo * sp.Blu[l] - nup * sp.Bul[l]);
+        double kap = 0.0, S = 0.0;
+        if (kchi > 0.0) {
+            double dnu = nu_ * cell[p].vw / kC;
+            kap = kchi / (kSqrtPi * dnu);
+            S = keta / kchi;
+        } else if (maser) {
+            atomicAdd(maser, 1ull);
+        }
+        if (F32)
+            reinterpret_cast<float2 *>(lc)[p * nl + l] = make_float2((float)kap, (float)S);
+        else
+            reinterpret_cast<double2 *>(lc)[p * nl + l] = make_double2(kap, S);
+        if (far) {
+            // (NaN or infinite values compare false or exceed every bound in far_segment)
+            const double I = ibdy[l];
+            const int eI = I > 0.0 ? __builtin_amdgcn_frexp_exp(I) : -1000000;
+            const float ek = kap == 0.0 ? -3000.0f : (isfinite(kap) ? (float)__builtin_amdgcn_frexp_exp(kap) : 1e9f);
+            const float es = S == 0.0 ? 0.0f : (isfinite(S) ? (float)(__builtin_amdgcn_frexp_exp(S) - eI + 1) : 1e9f);
+            s_far[threadIdx.x] = make_float2(ek, fmaxf(es, 0.0f));
+        }
     }
-    if (F32)
-        reinterpret_cast<float2 *>(lc)[q] = make_float2((float)kap, (float)S);
-    else
-        reinterpret_cast<double2 *>(lc)[q] = make_double2(kap, S);
+    if (!far) return;
+    __syncthreads();
+    if (on && l == 0) {
+        float2 f = s_far[threadIdx.x];
+        for (int i = 1; i < nl; ++i) {
+            const float2 v = s_far[threadIdx.x + i];
+            f.x = fmaxf(f.x, v.x);
+            f.y = fmaxf(f.y, v.y);
+        }
+        far[p] = f;
+    }
 }
 
-hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops,
-                            int64_t P, int fp32, void *lc, int64_t *maser_count, hipStream_t s)
+hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops, int64_t P, int fp32,
+                            void *lc, int64_t *maser_count, const double *ibdy, float2 *far, hipStream_t s)
 {
-    int64_t n = P * sp.n_lines;
-    if (n == 0) return hipSuccess;
-    dim3 grid((unsigned)((n + 255) / 256));
+    if (P * sp.n_lines == 0) return hipSuccess;
+    const int per_block = 256 / sp.n_lines;
+    dim3 grid((unsigned)((P + per_block - 1) / per_block));
     auto *m = reinterpret_cast<unsigned long long *>(maser_count);
     if (fp32)
-        hipLaunchKernelGGL(k_line_coef<true>, grid, dim3(256), 0, s, sp, cell, pops, P, lc, m);
+        hipLaunchKernelGGL(k_line_coef<true>, grid, dim3(256), 0, s, sp, cell, pops, P, lc, m, ibdy, far);
     else
-        hipLaunchKernelGGL(k_line_coef<false>, grid, dim3(256), 0, s, sp, cell, pops, P, lc, m);
+        hipLaunchKernelGGL(k_line_coef<false>, grid, dim3(256), 0, s, sp, cell, pops, P, lc, m, ibdy, far);
     return hipGetLastError();
 }
 

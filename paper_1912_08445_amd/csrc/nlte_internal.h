@@ -62,6 +62,7 @@ struct ConvResult {
 struct SolveArgs {
     const CellRec *cell;
     const void *lc;          // [P][n_lines] (kappa, S): double2 (FP64) or float2 (FP32 bulk)
+    const float2 *far;       // [P] log2 of the largest kappa and S / I_bdy of a cell's lines (see k_line_coef)
     const int64_t *roff;     // [P * n_rays + 1]
     const int32_t *rcells;   // cached walks, global point indices, nearest first
     const double *dir;       // [n_rays][3]
@@ -80,7 +81,7 @@ struct SolveArgs {
     int fchunks;             // frequency chunks per wave (n_q > 64), else 1
     int ns;                  // ray nodes a wave stages in LDS per round (2..64)
     int waves;               // register budget of the launch: 2 or 3 waves per SIMD
-    int collapse;            // 1: long-segment mode (profile recurrence, far-wing collapse)
+    int collapse;            // 1: long-segment mode (profile recurrence)
     int persistent;          // 1: items from the work counter in decreasing-cost order
     int tile;                // work items a workgroup takes at a time (1..16)
     int64_t n_blocks;        // work items (P * groups)
@@ -285,6 +286,7 @@ struct nlte_ctx {
 
     // work buffers (sized for P)
     void *d_lc = nullptr;  // line coefficients
+    float2 *d_far = nullptr;  // [P] bounds of the far-wing test
     double *d_pops_a = nullptr, *d_pops_b = nullptr;
     double *d_J = nullptr, *d_Jeff = nullptr, *d_L = nullptr;
     uint8_t *d_flags = nullptr;
@@ -387,7 +389,8 @@ hipError_t launch_walk_fill(const CellRec *cell, const NbrEntry *tab, int k, con
 hipError_t scan_lengths(int64_t *len_then_off, int64_t n, void *tmp, size_t *tmp_bytes,
                         hipStream_t s);
 hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops,
-                            int64_t P, int fp32, void *lc, int64_t *maser_count, hipStream_t s);
+                            int64_t P, int fp32, void *lc, int64_t *maser_count, const double *ibdy, float2 *far,
+                            hipStream_t s);
 hipError_t launch_formal_solve(const SolveArgs &a, const SolveConfig &cfg, int fp32, hipStream_t s);
 hipError_t launch_formal_solve_f64(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s);
 hipError_t launch_formal_solve_f32(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s);
