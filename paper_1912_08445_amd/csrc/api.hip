@@ -1223,6 +1223,9 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
                 box[6 * m + 3 + d] = hi[d] - lo[d];
             }
         }
+        c->extent = 0.0;
+        for (int m = 0; m < n_models; ++m)
+            for (int d = 0; d < 3; ++d) c->extent = std::max(c->extent, box[6 * m + 3 + d]);
         double *d_box = nullptr;
         if ((st2 = dalloc(c, &d_box, box.size()))) return st2;
         if ((st2 = dalloc(c, &c->d_morton, P))) {
@@ -1395,56 +1398,64 @@ nlte_status nlte_trace(nlte_ctx *c)
     if (st) return st;
     (void)hipSetDevice(c->device);
     const int64_t n = c->P * c->n_rays;
+    c->traced = false;   // until the new walks are complete
     if ((st = dalloc(c, &c->d_roff, n + 1))) return st;
     hipStream_t s = c->stream;
     HIPCHK(c, hipMemsetAsync(c->d_roff, 0, sizeof(int64_t), s));
     auto t0 = std::chrono::steady_clock::now();
-    // neighbour slots with their positions, for the walks only (freed on every return)
+    // neighbour slots, for the walks only (freed on every return)
     struct TabGuard {
-        NbrEntry *p = nullptr;
+        NbrSlot *p = nullptr;
         ~TabGuard() { dfree(p); }
     } tab;
-    if ((st = dalloc(c, &tab.p, (size_t)(c->P * c->k)))) return st;
-    HIPCHK(c, launch_nbr_table(c->d_cell, c->d_nbr, c->k, c->P, tab.p, s));
-    HIPCHK(c, launch_walk_count(c->d_cell, tab.p, c->k, c->d_bnd, c->d_dir, c->n_rays, c->P,
-                                c->d_roff + 1, s));
+    WalkArgs w{};
+    w.kp = (c->k + 3) / 4 * 4;
+    if ((st = dalloc(c, &tab.p, (size_t)c->P * w.kp))) return st;
+    if ((st = dalloc(c, &c->d_cost, c->P))) return st;
+    if ((st = dalloc(c, &c->d_order, c->P))) return st;
+    w.cell = c->d_cell;
+    w.tab = tab.p;
+    w.bnd = c->d_bnd;
+    w.dir = c->d_dir;
+    w.order = c->d_morton;
+    // a power of two scales without rounding; a model of no extent has nothing to walk to
+    w.inv_extent = c->extent > 0.0 && std::isfinite(c->extent) ? ldexp(1.0, -ilogb(c->extent)) : 1.0;
+    w.f_sub = c->params.f_sub;
+    w.P = c->P;
+    w.n_rays = c->n_rays;
+    unsigned long long *cost = c->d_cost;
+    auto *sums = reinterpret_cast<unsigned long long *>(c->d_conv);   // two words of the report's buffer
+    HIPCHK(c, hipMemsetAsync(cost, 0, sizeof(unsigned long long) * c->P, s));
+    HIPCHK(c, hipMemsetAsync(sums, 0, 2 * sizeof(unsigned long long), s));
+    HIPCHK(c, launch_nbr_slots(c->d_cell, c->d_nbr, c->k, w.kp, c->P, w.inv_extent, tab.p, s));
+    HIPCHK(c, launch_walk_count(w, c->d_roff + 1, cost, s));
+    HIPCHK(c, launch_trace_sums(c->d_roff + 1, n, cost, c->P, sums, s));
     size_t tmp_bytes = 0;
     HIPCHK(c, scan_lengths(c->d_roff, n, nullptr, &tmp_bytes, s));
     void *tmp = nullptr;
     HIPCHK(c, hipMalloc(&tmp, tmp_bytes ? tmp_bytes : 1));
     hipError_t e = scan_lengths(c->d_roff, n, tmp, &tmp_bytes, s);
+    // cells in all, the longest ray, and the costs (each ray counts one more than its steps)
+    int64_t total = 0;
+    unsigned long long h_sums[2] = {0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(&total, c->d_roff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(h_sums, sums, sizeof h_sums, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(tmp);
     if (e != hipSuccess) return fail(c, NLTE_E_HIP, std::string("scan: ") + hipGetErrorString(e));
-    int64_t total = 0;
-    HIPCHK(c, hipMemcpy(&total, c->d_roff + n, sizeof(int64_t), hipMemcpyDeviceToHost));
     if ((st = dalloc(c, &c->d_rcells, (size_t)total))) return st;
-    HIPCHK(c, launch_walk_fill(c->d_cell, tab.p, c->k, c->d_bnd, c->d_dir, c->n_rays, c->P,
-                               c->d_roff, c->d_rcells, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, launch_walk_fill(w, c->d_roff, c->d_rcells, s));
+    // the points in decreasing-cost order for the persistent formal solve
+    e = sort_by_cost(cost, c->d_order, c->P, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(c, NLTE_E_HIP, std::string("trace: ") + hipGetErrorString(e));
     dfree(tab.p);
     auto t1 = std::chrono::steady_clock::now();
     c->st_trace.ms += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st_trace.launches += 1;
-    // longest ray
-    std::vector<int64_t> off(n + 1);
-    HIPCHK(c, hipMemcpy(off.data(), c->d_roff, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost));
-    int mx = 0;
-    for (int64_t i = 0; i < n; ++i) mx = std::max<int>(mx, (int)(off[i + 1] - off[i]));
     c->total_cells = total;
-    c->max_len = mx;
-    // elimination steps per frequency (cells + velocity sub-steps), per-point cost and
-    // the points in decreasing-cost order for the persistent formal solve
-    if ((st = dalloc(c, &c->d_cost, c->P))) return st;
-    if ((st = dalloc(c, &c->d_order, c->P))) return st;
-    unsigned long long *cost = c->d_cost;
-    hipError_t e2 = hipMemsetAsync(cost, 0, sizeof(unsigned long long) * c->P, s);
-    if (e2 == hipSuccess) e2 = hipMemsetAsync(c->d_maser, 0, sizeof(int64_t), s);
-    SolveArgs a = solve_args(c, nullptr, nullptr, nullptr);
-    if (e2 == hipSuccess) e2 = launch_count_steps(a, c->d_maser, cost, s);
-    if (e2 == hipSuccess) e2 = hipMemcpyAsync(&c->total_steps, c->d_maser, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e2 == hipSuccess) e2 = sort_by_cost(cost, c->d_order, c->P, s);
-    if (e2 != hipSuccess) return fail(c, NLTE_E_HIP, std::string("step count: ") + hipGetErrorString(e2));
+    c->max_len = (int)h_sums[0];
+    c->total_steps = (int64_t)h_sums[1] - n;
     drop_graphs(c);
     c->traced = true;
     c->first_valid = false;

@@ -114,57 +114,4 @@ hipError_t launch_formal_solve(const SolveArgs &a, const SolveConfig &cfg, int f
     return fp32 ? launch_formal_solve_f32(a, cfg, s) : launch_formal_solve_f64(a, cfg, s);
 }
 
-// Elimination steps per frequency over all half rays: the cells of every cached walk
-// plus their velocity sub-steps, with the same sub-step rule as the sweep.  One thread
-// per (point, ray); block sums are added atomically (integer, order-independent).
-__global__ __launch_bounds__(256) void k_count_steps(SolveArgs a, unsigned long long *steps,
-                                                     unsigned long long *point_cost)
-{
-    __shared__ unsigned long long part[256];
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    unsigned long long n = 0;
-    if (q < a.P * a.n_rays) {
-        const int64_t O = q / a.n_rays;
-        const int ray = (int)(q - O * a.n_rays);
-        const double nx = a.dir[3 * ray], ny = a.dir[3 * ray + 1], nz = a.dir[3 * ray + 2];
-        const CellRec cO = a.cell[O];
-        const int64_t beg = a.roff[q];
-        const int L = (int)(a.roff[q + 1] - beg);
-        double s_prev = 0.0, w_prev = cO.vw;   // start at O and walk outward
-        for (int i = 0; i < L; ++i) {
-            const CellRec c = a.cell[a.rcells[beg + i]];
-            double dvx = c.vx - cO.vx, dvy = c.vy - cO.vy, dvz = c.vz - cO.vz;
-            double sv = (dvx * nx + dvy * ny) + dvz * nz;
-            double ds = fabs(sv - s_prev);
-            double thr = a.f_sub * fmin(c.vw, w_prev);
-            unsigned long long m = 1;
-            if (ds > thr) {
-                const double mr = ceil(ds / thr);
-                m = mr < (double)kMaxSub ? (unsigned long long)mr : (unsigned long long)kMaxSub;
-            }
-            n += m;
-            s_prev = sv;
-            w_prev = c.vw;
-        }
-        if (point_cost != nullptr) atomicAdd(&point_cost[O], n + 1);
-    }
-    part[threadIdx.x] = n;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(steps, part[0]);
-}
-
-hipError_t launch_count_steps(const SolveArgs &a, int64_t *steps, unsigned long long *point_cost,
-                              hipStream_t s)
-{
-    const int64_t n = a.P * a.n_rays;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_steps, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a,
-                       reinterpret_cast<unsigned long long *>(steps), point_cost);
-    return hipGetLastError();
-}
-
 }  // namespace nlte

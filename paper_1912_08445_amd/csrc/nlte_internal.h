@@ -249,6 +249,7 @@ struct nlte_ctx {
     int32_t *d_model_of = nullptr;  // [P]
     int64_t *d_model_off = nullptr; // [n_models + 1]
     int32_t *d_morton = nullptr;    // [P] points in Morton order within each model
+    double extent = 1.0;            // largest side of the models' bounding boxes
     uint8_t *d_model_done = nullptr;            // [n_models]
     unsigned long long *d_model_change = nullptr;  // [n_models] max change as FP64 bits
     int32_t *d_model_iters = nullptr;           // [n_models]
@@ -372,20 +373,29 @@ hipError_t launch_setup_points(const double *pos, const double *vel, const doubl
                                double mass, int64_t P, CellRec *cell, hipStream_t s);
 hipError_t launch_lte(const SpeciesDev &sp, const CellRec *cell, const double *T, int64_t P,
                       double *pops, hipStream_t s);
-// Neighbour slot of a point for the ray walk: the neighbour's position and index (m < 0:
-// an unused slot), k slots per point back to back.
-struct __align__(32) NbrEntry {
-    double x, y, z;
-    int32_t m, pad;
+// Neighbour slot of a cell for the ray walk: the neighbour's offset in units of the model's
+// extent (see k_walk) and its index (m < 0: an unused slot).
+struct __align__(16) NbrSlot {
+    float x, y, z;
+    int32_t m;
 };
-hipError_t launch_nbr_table(const CellRec *cell, const int32_t *nbr, int k, int64_t P, NbrEntry *tab,
-                            hipStream_t s);
-hipError_t launch_walk_count(const CellRec *cell, const NbrEntry *tab, int k, const uint8_t *bnd,
-                             const double *dir, int n_rays, int64_t P, int64_t *len,
-                             hipStream_t s);
-hipError_t launch_walk_fill(const CellRec *cell, const NbrEntry *tab, int k, const uint8_t *bnd,
-                            const double *dir, int n_rays, int64_t P, const int64_t *off,
-                            int32_t *cells, hipStream_t s);
+struct WalkArgs {
+    const CellRec *cell;
+    const NbrSlot *tab;      // [P][kp]
+    const uint8_t *bnd;      // boundary flags (null: none)
+    const double *dir;       // [n_rays][3]
+    const int32_t *order;    // [P] points in Morton order
+    double inv_extent;       // power of two, 1 / extent of the model(s)
+    double f_sub;
+    int64_t P;
+    int n_rays, kp;
+};
+hipError_t launch_nbr_slots(const CellRec *cell, const int32_t *nbr, int k, int kp, int64_t P, double inv_extent,
+                            NbrSlot *tab, hipStream_t s);
+hipError_t launch_walk_count(const WalkArgs &a, int64_t *len, unsigned long long *cost, hipStream_t s);
+hipError_t launch_walk_fill(const WalkArgs &a, const int64_t *off, int32_t *cells, hipStream_t s);
+hipError_t launch_trace_sums(const int64_t *len, int64_t n, const unsigned long long *cost, int64_t P,
+                             unsigned long long *out, hipStream_t s);
 hipError_t scan_lengths(int64_t *len_then_off, int64_t n, void *tmp, size_t *tmp_bytes,
                         hipStream_t s);
 hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops,
@@ -402,8 +412,6 @@ size_t formal_solve_lds_f32(int lpl, int ns);
 constexpr size_t kFsStaticLds = 256;
 constexpr size_t kLdsGranule = 512;
 hipError_t launch_formal_solve_band(const SolveArgs &a, hipStream_t s);
-hipError_t launch_count_steps(const SolveArgs &a, int64_t *steps, unsigned long long *point_cost,
-                              hipStream_t s);
 hipError_t sort_by_cost(unsigned long long *cost, int32_t *order, int64_t P, hipStream_t s);
 hipError_t morton_order(const CellRec *cell, const int32_t *model_of, const double *box, const int64_t *off,
                         int n_models, int64_t P, int32_t *order, hipStream_t s);
