@@ -295,14 +295,13 @@ nlte_status stateq_impl(nlte_ctx *c, const double *d_old, const double *d_J, con
                         const double *d_L, double *d_new, uint8_t *d_flags, ConvResult *d_conv,
                         hipStream_t s, bool ali = false, bool capture = false)
 {
-    const int64_t nb = stateq_blocks(c->P);
     auto sq = [&] {
         return launch_stateq(c->sp, c->d_cell, c->d_nh2, c->d_T, c->P, c->params.use_alo, d_old, d_J, d_Jeff,
-                             d_L, d_new, d_flags, c->d_partials, nb, ali ? c->d_model_done : nullptr,
+                             d_L, d_new, d_flags, c->d_partials, ali ? c->d_model_done : nullptr,
                              c->d_model_of, ali ? c->d_model_change : nullptr, s);
     };
     HIPCHK(c, capture ? sq() : timed(c, c->st_stateq, s, sq));
-    if (d_conv) HIPCHK(c, launch_conv_final(c->d_partials, nb, d_conv, s));
+    if (d_conv) HIPCHK(c, launch_conv_final(c->d_partials, stateq_blocks(c->P), d_conv, s));
     return NLTE_OK;
 }
 
@@ -729,7 +728,7 @@ nlte_status stateq_band_impl(nlte_ctx *c, const double *d_old, const double *d_J
     }
     auto local = [&](double *out, ConvPartial *parts, unsigned long long *change) {
         return launch_stateq(c->sp, c->d_cell, c->d_nh2, c->d_T, c->P, c->params.use_alo, d_old, d_J, d_Jeff, d_L,
-                             out, d_flags, parts, stateq_blocks(c->P), ali ? c->d_model_done : nullptr,
+                             out, d_flags, parts, ali ? c->d_model_done : nullptr,
                              c->d_model_of, change, s);
     };
     if (n_bad == c->n_models) {

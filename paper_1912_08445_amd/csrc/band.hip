@@ -221,7 +221,7 @@ __global__ void k_band_check_models(const double *__restrict__ x, int n, int64_t
 // New populations: the band's, or the local solve's for models marked in model_bad
 // (local and model_bad nullable: every model takes the band's); change statistics and
 // per-model changes as the local solve reports them.
-__global__ __launch_bounds__(256) void k_band_finish(const double *__restrict__ x, const double *__restrict__ local,
+__global__ __launch_bounds__(kWave) void k_band_finish(const double *__restrict__ x, const double *__restrict__ local,
                                                      const uint8_t *__restrict__ model_bad,
                                                      const double *__restrict__ old,
                                                      const CellRec *__restrict__ cell, int n, int64_t P,
@@ -230,11 +230,7 @@ __global__ __launch_bounds__(256) void k_band_finish(const double *__restrict__ 
                                                      const int32_t *__restrict__ model_of,
                                                      unsigned long long *__restrict__ model_change)
 {
-    __shared__ double s_max[256], s_sum[256];
-    __shared__ int64_t s_cnt[256];
-    __shared__ int s_one_model;
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (threadIdx.x == 0) s_one_model = block_in_one_model(model_of, P);
     double mx = 0.0, sum = 0.0;
     int64_t cnt = 0;
     if (p < P) {
@@ -254,33 +250,7 @@ __global__ __launch_bounds__(256) void k_band_finish(const double *__restrict__ 
         }
         if (flags && !loc) flags[p] = 0;   // the local solve has set its own
     }
-    const int t = threadIdx.x;
-    s_max[t] = mx;
-    s_sum[t] = sum;
-    s_cnt[t] = cnt;
-    __syncthreads();
-    if (model_change != nullptr && !s_one_model && cnt > 0)
-        atomicMax(&model_change[model_of[p]], (unsigned long long)__double_as_longlong(mx));
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            s_max[t] = fmax(s_max[t], s_max[t + w]);
-            s_sum[t] += s_sum[t + w];
-            s_cnt[t] += s_cnt[t + w];
-        }
-        __syncthreads();
-    }
-    if (t == 0 && model_change != nullptr && s_one_model && s_cnt[0] > 0)
-        atomicMax(&model_change[model_of[blockIdx.x * (int64_t)blockDim.x]],
-                  (unsigned long long)__double_as_longlong(s_max[0]));
-    if (t == 0 && partials) {
-        ConvPartial cp;
-        cp.max_change = s_max[0];
-        cp.sum_change = s_sum[0];
-        cp.count = s_cnt[0];
-        cp.n_fallback = 0;
-        cp.n_kept = 0;
-        partials[blockIdx.x] = cp;
-    }
+    report_change(mx, sum, cnt, 0, 0, p, P, model_of, model_change, partials);
 }
 
 hipError_t launch_band_setup(const BandArgs &b, const SpeciesDev &sp, const CellRec *cell, const double *nh2,
@@ -344,7 +314,7 @@ hipError_t launch_band_finish(const double *x, const double *local, const uint8_
                               unsigned long long *model_change, hipStream_t s)
 {
     if (P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_band_finish, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, x, local, model_bad, old,
+    hipLaunchKernelGGL(k_band_finish, dim3((unsigned)stateq_blocks(P)), dim3(kWave), 0, s, x, local, model_bad, old,
                        cell, n, P, pops_new, flags, partials, done, model_of, model_change);
     return hipGetLastError();
 }

@@ -422,8 +422,7 @@ hipError_t launch_model_update(int n_models, unsigned long long *change, uint8_t
 hipError_t launch_stateq(const SpeciesDev &sp, const CellRec *cell, const double *nh2,
                          const double *T, int64_t P, int use_alo, const double *pops_old,
                          const double *J, const double *Jeff, const double *L, double *pops_new,
-                         uint8_t *flags, ConvPartial *partials, int64_t n_blocks,
-                         const uint8_t *model_done, const int32_t *model_of,
+                         uint8_t *flags, ConvPartial *partials, const uint8_t *model_done, const int32_t *model_of,
                          unsigned long long *model_change, hipStream_t s);
 int64_t stateq_blocks(int64_t P);
 hipError_t launch_conv_final(const ConvPartial *partials, int64_t n, ConvResult *out,
