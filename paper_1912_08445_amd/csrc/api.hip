@@ -456,13 +456,13 @@ nlte_status mlp_ensure_points(nlte_ctx *c)
 nlte_status features_impl(nlte_ctx *c, double *d_F, hipStream_t s)
 {
     HIPCHK(c, timed(c, c->st_features, s, [&] {
-        return launch_features(c->d_cell, c->d_nh2, c->d_T, c->d_nbr, c->k, c->d_roff, c->d_rcells, c->d_dir,
+        return launch_features(c->d_cell, c->d_pn, c->d_T, c->d_nbr, c->k, c->d_roff, c->d_rcells, c->d_dir,
                                c->n_rays, c->P, d_F, s);
     }));
     return NLTE_OK;
 }
 
-// Features -> standardised inputs -> network (departures from LTE) -> populations, over LTE populations for
+// Features -> standardised inputs -> network (departures from LTE) -> populations, LTE for
 // points whose prediction is not finite.  The count of those lands in m.d_bad.
 nlte_status predict_impl(nlte_ctx *c, double *d_pops, hipStream_t s)
 {
@@ -470,11 +470,9 @@ nlte_status predict_impl(nlte_ctx *c, double *d_pops, hipStream_t s)
     nlte_status st;
     if ((st = mlp_ensure_points(c))) return st;
     if ((st = features_impl(c, m.d_feat, s))) return st;
-    HIPCHK(c, launch_mlp_standardise(m.d_feat, m.norm, c->P, m.d_xp, s));
+    HIPCHK(c, launch_mlp_standardise(m.d_feat, m.norm, c->P, m.d_xp, m.d_bad, s));
     HIPCHK(c, timed(c, c->st_mlp_forward, s,
                     [&] { return launch_mlp_forward(m.d_frags, m.d_theta, m.dims, m.d_xp, c->P, m.d_yp, s); }));
-    HIPCHK(c, launch_fill_u64(m.d_bad, 1, 0ull, s));
-    HIPCHK(c, launch_lte(c->sp, c->d_cell, c->d_T, c->P, d_pops, s));
     HIPCHK(c, launch_mlp_populations(c->sp, m.d_yp, c->d_cell, c->d_T, c->P, d_pops, m.d_bad, s));
     return NLTE_OK;
 }
@@ -917,6 +915,7 @@ void nlte_destroy(nlte_ctx *c)
     dfree(c->d_exec);
     dfree(c->d_species_mem);
     dfree(c->d_cell);
+    dfree(c->d_pn);
     dfree(c->d_nh2);
     dfree(c->d_T);
     dfree(c->d_nbr);
@@ -1152,7 +1151,7 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
     // device copies
     double *d_pos = nullptr, *d_vel = nullptr, *d_vt = nullptr, *d_X = nullptr;
     nlte_status st;
-    if ((st = dalloc(c, &c->d_cell, P)) || (st = dalloc(c, &c->d_nh2, P)) || (st = dalloc(c, &c->d_T, P)) ||
+    if ((st = dalloc(c, &c->d_cell, P)) || (st = dalloc(c, &c->d_pn, P)) || (st = dalloc(c, &c->d_nh2, P)) || (st = dalloc(c, &c->d_T, P)) ||
         (st = dalloc(c, &c->d_nbr, P * (size_t)k)) || (st = dalloc(c, &d_pos, 3 * P)) ||
         (st = dalloc(c, &d_vel, 3 * P)) || (st = dalloc(c, &d_vt, P)) || (st = dalloc(c, &d_X, P))) {
         dfree(d_pos);
@@ -1178,7 +1177,7 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
         cp(c->d_bnd, boundary, P);
     }
     if (e == hipSuccess)
-        e = launch_setup_points(d_pos, d_vel, c->d_nh2, c->d_T, d_vt, d_X, c->mass, P, c->d_cell, c->stream);
+        e = launch_setup_points(d_pos, d_vel, c->d_nh2, c->d_T, d_vt, d_X, c->mass, P, c->d_cell, c->d_pn, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     dfree(d_pos);
     dfree(d_vel);
@@ -2229,7 +2228,7 @@ nlte_status nlte_mlp_rows_dev(nlte_ctx *c, const double *d_pops, float *d_X, flo
     if ((st = mlp_ensure_points(c))) return st;
     hipStream_t s = pick(c, stream);
     if ((st = features_impl(c, c->mlp.d_feat, s))) return st;
-    HIPCHK(c, launch_mlp_standardise(c->mlp.d_feat, c->mlp.norm, c->P, d_X, s));
+    HIPCHK(c, launch_mlp_standardise(c->mlp.d_feat, c->mlp.norm, c->P, d_X, nullptr, s));
     HIPCHK(c, launch_mlp_targets(c->sp, d_pops, c->d_cell, c->d_T, c->P, d_T, s));
     return NLTE_OK;
 }

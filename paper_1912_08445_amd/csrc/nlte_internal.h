@@ -255,6 +255,7 @@ struct nlte_ctx {
     int32_t *d_model_iters = nullptr;           // [n_models]
     double *d_model_last = nullptr;             // [n_models]
     nlte::CellRec *d_cell = nullptr;
+    double4 *d_pn = nullptr;   // [P] position and H2 density of each cell, one 32-byte gather
     double *d_nh2 = nullptr, *d_T = nullptr;
     int32_t *d_nbr = nullptr;  // global indices
     uint8_t *d_bnd = nullptr;
@@ -370,7 +371,8 @@ __device__ inline int block_in_one_model(const int32_t *model_of, int64_t P)
 // Launchers (each enqueues on `stream`; return hipSuccess or the launch error).
 hipError_t launch_setup_points(const double *pos, const double *vel, const double *nh2,
                                const double *T, const double *vturb, const double *X,
-                               double mass, int64_t P, CellRec *cell, hipStream_t s);
+                               double mass, int64_t P, CellRec *cell, double4 *pn,
+                               hipStream_t s);
 hipError_t launch_lte(const SpeciesDev &sp, const CellRec *cell, const double *T, int64_t P,
                       double *pops, hipStream_t s);
 // Neighbour slot of a cell for the ray walk: the neighbour's offset in units of the model's
@@ -459,7 +461,7 @@ hipError_t launch_ng(const NgHist &h, const CellRec *cell, const int64_t *off, c
                      uint8_t *ok, double *out, unsigned long long *rejected, hipStream_t s);
 
 // warm start
-hipError_t launch_features(const CellRec *cell, const double *nh2, const double *T, const int32_t *nbr,
+hipError_t launch_features(const CellRec *cell, const double4 *pn, const double *T, const int32_t *nbr,
                            int k, const int64_t *roff, const int32_t *rcells, const double *dir, int R,
                            int64_t P, double *F, hipStream_t s);
 int mlp_frag_count();
@@ -478,7 +480,8 @@ hipError_t launch_mlp_train(const void *frags, const float *theta, const MlpDims
 hipError_t launch_mlp_update(float *theta, float *m, float *v, void *frags, const MlpDims &d, const float *gpart,
                              int batch, int update, float lr, float b1, float b2, float eps, float c1, float c2,
                              const float *lpart, float inv_count, float *loss, float *grad_out, hipStream_t s);
-hipError_t launch_mlp_standardise(const double *F, const MlpNorm &nm, int64_t P, float *X, hipStream_t s);
+hipError_t launch_mlp_standardise(const double *F, const MlpNorm &nm, int64_t P, float *X, unsigned long long *n_bad,
+                                  hipStream_t s);
 hipError_t launch_mlp_targets(const SpeciesDev &sp, const double *pops, const CellRec *cell, const double *T,
                               int64_t P, float *Tg, hipStream_t s);
 hipError_t launch_mlp_populations(const SpeciesDev &sp, const float *Y, const CellRec *cell, const double *T,

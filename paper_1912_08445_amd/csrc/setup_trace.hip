@@ -13,7 +13,7 @@ namespace nlte {
 __global__ void k_setup_points(const double *__restrict__ pos, const double *__restrict__ vel,
                                const double *__restrict__ nh2, const double *__restrict__ T,
                                const double *__restrict__ vturb, const double *__restrict__ X,
-                               double mass, int64_t P, CellRec *__restrict__ cell)
+                               double mass, int64_t P, CellRec *__restrict__ cell, double4 *__restrict__ pn)
 {
     int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p >= P) return;
@@ -28,16 +28,17 @@ __global__ void k_setup_points(const double *__restrict__ pos, const double *__r
     c.vw = sqrt(vth2 + vturb[p] * vturb[p]);
     c.ntot = X[p] * nh2[p];
     cell[p] = c;
+    pn[p] = make_double4(c.px, c.py, c.pz, nh2[p]);
 }
 
 hipError_t launch_setup_points(const double *pos, const double *vel, const double *nh2,
                                const double *T, const double *vturb, const double *X,
-                               double mass, int64_t P, CellRec *cell, hipStream_t s)
+                               double mass, int64_t P, CellRec *cell, double4 *pn, hipStream_t s)
 {
     if (P == 0) return hipSuccess;
     int64_t blocks = (P + 255) / 256;
     hipLaunchKernelGGL(k_setup_points, dim3((unsigned)blocks), dim3(256), 0, s, pos, vel, nh2, T,
-                       vturb, X, mass, P, cell);
+                       vturb, X, mass, P, cell, pn);
     return hipGetLastError();
 }
 

@@ -96,71 +96,95 @@ __device__ inline Frag load_frag(const Frag *base, int idx, int lane) { return b
 
 // ------------------------------------------------------------------------- features
 
+// v of the lane N places before this one in its row of 16 (the first lanes get the last ones')
+template <int N>
+__device__ __forceinline__ double row_ror(double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(w.x, 0x120 + N, 0xF, 0xF, true),
+                                                __builtin_amdgcn_mov_dpp(w.y, 0x120 + N, 0xF, 0xF, true)));
+}
+
 // One wave per point.  F[p][0..7]: log10 n_H2, log10 T, log10 of the mean velocity
 // gradient to the neighbours (floored at 1e-30 s^-1), and log10 of the minimum, quartiles
 // and maximum over the rays of the H2 column along the cached walk (trapezoid in the
 // projected distance, at least half a cell's column and 1 cm^-2).  Quantiles interpolate
-// linearly between order statistics at position q (n_rays - 1).  The lanes take a ray's
-// cells 64 at a time (coalesced reads of the walk cache), each forms its cell's trapezoid
-// term with the previous cell's values from its neighbour lane, and the wave sums the
-// terms.
-__global__ __launch_bounds__(64) void k_features(const CellRec *__restrict__ cell,
-                                                 const double *__restrict__ nh2,
-                                                 const double *__restrict__ T,
-                                                 const int32_t *__restrict__ nbr, int k,
-                                                 const int64_t *__restrict__ roff,
-                                                 const int32_t *__restrict__ rcells,
+// linearly between order statistics at position q (n_rays - 1).
+//
+// Four rays at a time, 16 lanes each: the lanes take a ray's cells 16 at a time, each forms
+// its cell's trapezoid term with the previous cell's values from the lane before (moves
+// within a row of 16) and the row adds its terms.  Bound by the gathers of the cells: their
+// position and density come as one 32-byte record (pn, 1.3 MB for 40,009 points, which an
+// XCD's L2 holds) instead of two cache lines of the 64-byte records and the density array.
+// The neighbours' distances and gradients take a lane each, and the eight logarithms too.
+// Disc of 40,009 points with 48 rays (78 M cells): 0.56 ms, 4.5 cycles of a CU per cell, near
+// what filling a 128-byte line for each takes; one ray per wave at a time, all lanes on the
+// neighbours and one on the logarithms, took 0.99 ms.
+__global__ __launch_bounds__(64) void k_features(const CellRec *__restrict__ cell, const double4 *__restrict__ pn,
+                                                 const double *__restrict__ T, const int32_t *__restrict__ nbr, int k,
+                                                 const int64_t *__restrict__ roff, const int32_t *__restrict__ rcells,
                                                  const double *__restrict__ dir, int R, int64_t P,
                                                  double *__restrict__ F)
 {
     extern __shared__ double sh[];
     double *col = sh;
     double *srt = sh + R;
+    __shared__ double nb_dist[64], nb_grad[64];
     const int64_t p = blockIdx.x;
     const int lane = threadIdx.x;
     if (p >= P) return;
-    const double ox = cell[p].px, oy = cell[p].py, oz = cell[p].pz;
+    const double4 o = pn[p];
+    // neighbours: distance and velocity gradient of slot `lane` (k <= 64)
+    int32_t m = lane < k ? nbr[p * k + lane] : -1;
+    if (m >= 0) {
+        const CellRec c = cell[m], own = cell[p];
+        const double dvx = c.vx - own.vx, dvy = c.vy - own.vy, dvz = c.vz - own.vz;
+        const double dx = c.px - o.x, dy = c.py - o.y, dz = c.pz - o.z;
+        const double nx = sqrt((dx * dx + dy * dy) + dz * dz);
+        nb_dist[lane] = nx;
+        nb_grad[lane] = sqrt((dvx * dvx + dvy * dvy) + dvz * dvz) / nx;
+    }
+    const unsigned long long used = __ballot(m >= 0);
+    __syncthreads();
+    double dsum = 0.0, gsum = 0.0;
+    for (unsigned long long u = used; u != 0; u &= u - 1) {   // in slot order
+        const int s = (int)__builtin_ctzll(u);
+        dsum += nb_dist[s];
+        gsum += nb_grad[s];
+    }
+    const int count = (int)__builtin_popcountll(used);
     // half a cell's column, the least a ray's column is taken to be (a walk with no cell
     // lies at the model's edge): n_H2 times half the mean distance to the neighbours
-    double dsum = 0.0;
-    int dcount = 0;
-    for (int s = 0; s < k; ++s) {
-        const int32_t m = nbr[p * k + s];
-        if (m < 0) continue;
-        const double dx = cell[m].px - ox, dy = cell[m].py - oy, dz = cell[m].pz - oz;
-        dsum += sqrt((dx * dx + dy * dy) + dz * dz);
-        ++dcount;
-    }
-    const double half_cell = dcount > 0 ? 0.5 * nh2[p] * (dsum / dcount) : 0.0;
+    const double half_cell = count > 0 ? 0.5 * o.w * (dsum / count) : 0.0;
     const double floor_col = half_cell > 1.0 ? half_cell : 1.0;
 
-    const double n_O = nh2[p];
-    for (int r = 0; r < R; ++r) {
+    const int sub = lane & 15;
+    for (int r = lane >> 4; r < R; r += 4) {
         const double nx = dir[3 * r], ny = dir[3 * r + 1], nz = dir[3 * r + 2];
         const int64_t b = roff[p * R + r];
         const int L = (int)(roff[p * R + r + 1] - b);
         // trapezoid terms 0.5 (n_{i-1} + n_i)(Z_i - Z_{i-1}) from the point (n_O, Z = 0) on
-        double acc = 0.0, n_carry = n_O, z_carry = 0.0;
-        for (int i0 = 0; i0 < L; i0 += 64) {
-            const int i = i0 + lane;
+        double acc = 0.0, n_carry = o.w, z_carry = 0.0;
+        for (int i0 = 0; i0 < L; i0 += 16) {
+            const int i = i0 + sub;
             double Z = 0.0, n_i = 0.0;
             if (i < L) {
-                const int32_t c = rcells[b + i];
-                const double dx = cell[c].px - ox, dy = cell[c].py - oy, dz = cell[c].pz - oz;
+                const double4 c = pn[rcells[b + i]];
+                const double dx = c.x - o.x, dy = c.y - o.y, dz = c.z - o.z;
                 Z = (dx * nx + dy * ny) + dz * nz;
-                n_i = nh2[c];
+                n_i = c.w;
             }
-            double n_prev = __shfl_up(n_i, 1), z_prev = __shfl_up(Z, 1);
-            if (lane == 0) {
-                n_prev = n_carry;
-                z_prev = z_carry;
-            }
+            const double n_rot = row_ror<1>(n_i), z_rot = row_ror<1>(Z);   // lane 0: the last of these cells
+            const double n_prev = sub == 0 ? n_carry : n_rot, z_prev = sub == 0 ? z_carry : z_rot;
             if (i < L) acc += 0.5 * (n_prev + n_i) * (Z - z_prev);
-            n_carry = __shfl(n_i, 63);
-            z_carry = __shfl(Z, 63);
+            n_carry = n_rot;
+            z_carry = z_rot;
         }
-        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-        if (lane == 0) col[r] = acc > floor_col ? acc : floor_col;
+        acc += row_ror<8>(acc);
+        acc += row_ror<4>(acc);
+        acc += row_ror<2>(acc);
+        acc += row_ror<1>(acc);
+        if (sub == 0) col[r] = acc > floor_col ? acc : floor_col;
     }
     __syncthreads();
     // order statistics: rank by value, equal values by ray index
@@ -174,40 +198,31 @@ __global__ __launch_bounds__(64) void k_features(const CellRec *__restrict__ cel
         srt[rank] = v;
     }
     __syncthreads();
-    if (lane != 0) return;
-    double *f = F + 8 * p;
-    f[0] = log10(nh2[p]);
-    f[1] = log10(T[p]);
-    double gsum = 0.0;
-    int gcount = 0;
-    for (int s = 0; s < k; ++s) {
-        const int32_t m = nbr[p * k + s];
-        if (m < 0) continue;
-        const double dvx = cell[m].vx - cell[p].vx, dvy = cell[m].vy - cell[p].vy, dvz = cell[m].vz - cell[p].vz;
-        const double dx = cell[m].px - ox, dy = cell[m].py - oy, dz = cell[m].pz - oz;
-        const double nv = sqrt((dvx * dvx + dvy * dvy) + dvz * dvz);
-        const double nx = sqrt((dx * dx + dy * dy) + dz * dz);
-        gsum += nv / nx;
-        ++gcount;
-    }
-    const double g = gcount > 0 ? gsum / gcount : 0.0;
-    f[2] = log10(g > 1e-30 ? g : 1e-30);
-    const double qs[5] = {0.0, 0.25, 0.5, 0.75, 1.0};
-    for (int j = 0; j < 5; ++j) {
-        const double h = qs[j] * (R - 1);
+    if (lane >= 8) return;
+    double v;
+    if (lane == 0) {
+        v = o.w;
+    } else if (lane == 1) {
+        v = T[p];
+    } else if (lane == 2) {
+        const double g = count > 0 ? gsum / count : 0.0;
+        v = g > 1e-30 ? g : 1e-30;
+    } else {
+        const double h = 0.25 * (lane - 3) * (R - 1);
         const int i = (int)floor(h);
-        double v = srt[i];
+        v = srt[i];
         if (i + 1 < R) v = srt[i] + (h - i) * (srt[i + 1] - srt[i]);
-        f[3 + j] = log10(v);
     }
+    F[8 * p + lane] = log10(v);
 }
 
-hipError_t launch_features(const CellRec *cell, const double *nh2, const double *T, const int32_t *nbr,
+hipError_t launch_features(const CellRec *cell, const double4 *pn, const double *T, const int32_t *nbr,
                            int k, const int64_t *roff, const int32_t *rcells, const double *dir, int R,
                            int64_t P, double *F, hipStream_t s)
 {
     if (P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_features, dim3((unsigned)P), dim3(64), sizeof(double) * 2 * R, s, cell, nh2, T, nbr, k, roff, rcells, dir, R, P, F);
+    hipLaunchKernelGGL(k_features, dim3((unsigned)P), dim3(64), sizeof(double) * 2 * R, s, cell, pn, T, nbr, k, roff,
+                       rcells, dir, R, P, F);
     return hipGetLastError();
 }
 
@@ -774,19 +789,24 @@ hipError_t launch_mlp_update(float *theta, float *m, float *v, void *frags, cons
     return hipGetLastError();
 }
 
-// Standardised FP32 inputs from FP64 features.
-__global__ void k_mlp_standardise(const double *__restrict__ F, MlpNorm nm, int64_t P, float *__restrict__ X)
+// Standardised FP32 inputs from FP64 features; n_bad (nullable) is set to zero for the
+// prediction that follows.
+__global__ void k_mlp_standardise(const double *__restrict__ F, MlpNorm nm, int64_t P, float *__restrict__ X,
+                                  unsigned long long *__restrict__ n_bad)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t == 0 && n_bad) *n_bad = 0;
     if (t >= P * 8) return;
     const int f = (int)(t % 8);
     X[t] = (float)((F[t] - nm.mean[f]) / nm.std[f]);
 }
 
-hipError_t launch_mlp_standardise(const double *F, const MlpNorm &nm, int64_t P, float *X, hipStream_t s)
+hipError_t launch_mlp_standardise(const double *F, const MlpNorm &nm, int64_t P, float *X, unsigned long long *n_bad,
+                                  hipStream_t s)
 {
     if (P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_standardise, dim3((unsigned)((P * 8 + 255) / 256)), dim3(256), 0, s, F, nm, P, X);
+    hipLaunchKernelGGL(k_mlp_standardise, dim3((unsigned)((P * 8 + 255) / 256)), dim3(256), 0, s, F, nm, P, X,
+                       n_bad);
     return hipGetLastError();
 }
 
@@ -826,7 +846,10 @@ hipError_t launch_mlp_targets(const SpeciesDev &sp, const double *pops, const Ce
 
 // Populations from predicted departures y: n_i = ntot w_i / sum_j w_j with
 // w_i = f_i^LTE 10^y_i (evaluated relative to the largest log10 w).  A point with a
-// non-finite prediction keeps what pops already holds and is counted.
+// non-finite prediction takes its LTE populations and is counted.  The partition function and
+// the levels' Boltzmann factors are evaluated once per point (once per level and level they
+// took 25 us for 40,009 points of ten levels, after a kernel of 7 us for the LTE populations;
+// now 14 us with those).
 __global__ void k_mlp_populations(SpeciesDev sp, const float *__restrict__ Y, const CellRec *__restrict__ cell,
                                   const double *__restrict__ T, int64_t P, double *__restrict__ pops,
                                   unsigned long long *__restrict__ n_bad)
@@ -834,33 +857,50 @@ __global__ void k_mlp_populations(SpeciesDev sp, const float *__restrict__ Y, co
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p >= P) return;
     const int n_lev = sp.n_lev;
-    double a[kMaxLev];
+    const double kT = kKB * T[p], nt = cell[p].ntot;
+    double a[kMaxLev], e[kMaxLev];   // (indices known when compiled: registers)
+    double Z = 0.0;
+#pragma unroll
+    for (int i = 0; i < kMaxLev; ++i)
+        if (i < n_lev) {
+            e[i] = exp(-(sp.E[i] - sp.E[0]) / kT);
+            Z += sp.g[i] * e[i];
+        }
     double amax = -INFINITY;
     bool ok = true;
-    for (int i = 0; i < n_lev; ++i) {
-        const double y = (double)Y[p * n_lev + i];
-        ok = ok && isfinite(y);
-        a[i] = log10(lte_fraction(sp, T[p], i)) + y;
-        amax = fmax(amax, a[i]);
-    }
+#pragma unroll
+    for (int i = 0; i < kMaxLev; ++i)
+        if (i < n_lev) {
+            const double y = (double)Y[p * n_lev + i];
+            ok = ok && isfinite(y);
+            const double f = sp.g[i] * e[i] / Z;
+            a[i] = log10(f > 1e-300 ? f : 1e-300) + y;
+            amax = fmax(amax, a[i]);
+        }
     if (!ok) {
         atomicAdd(n_bad, 1ull);
+#pragma unroll
+        for (int i = 0; i < kMaxLev; ++i)
+            if (i < n_lev) pops[p * n_lev + i] = nt * sp.g[i] * e[i] / Z;
         return;
     }
     double sum = 0.0;
-    for (int i = 0; i < n_lev; ++i) {
-        a[i] = exp10(a[i] - amax);
-        sum += a[i];
-    }
-    const double nt = cell[p].ntot;
-    for (int i = 0; i < n_lev; ++i) pops[p * n_lev + i] = nt * a[i] / sum;
+#pragma unroll
+    for (int i = 0; i < kMaxLev; ++i)
+        if (i < n_lev) {
+            a[i] = exp10(a[i] - amax);
+            sum += a[i];
+        }
+#pragma unroll
+    for (int i = 0; i < kMaxLev; ++i)
+        if (i < n_lev) pops[p * n_lev + i] = nt * a[i] / sum;
 }
 
 hipError_t launch_mlp_populations(const SpeciesDev &sp, const float *Y, const CellRec *cell, const double *T,
                                   int64_t P, double *pops, unsigned long long *n_bad, hipStream_t s)
 {
     if (P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_populations, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, sp, Y, cell, T, P, pops,
+    hipLaunchKernelGGL(k_mlp_populations, dim3((unsigned)((P + 63) / 64)), dim3(64), 0, s, sp, Y, cell, T, P, pops,
                        n_bad);
     return hipGetLastError();
 }
