@@ -71,9 +71,10 @@ typedef struct {
                            register file, 512 with the accumulation registers; 3: 168);
                            0 = by rule (3 in the FP32 form and up to two lines per lane in
                            FP64, else 2).  0 */
-    int persistent;   /* 1: persistent formal solve taking points from a work queue in
-                         decreasing order of their cached step counts; 0: one workgroup per
-                         tile of points in index order (XCD-contiguous).  1 */
+    int persistent;   /* 1: formal solve in decreasing order of the points' cached step counts,
+                         the pairs of few points split over several workgroups; 0: one
+                         workgroup per tile of points in index order (XCD-contiguous).
+                         Results do not depend on it.  1 */
     int ng_every;     /* Ng acceleration (Sec. 3.4): after every ng_every regular ALI
                          iterations each model still iterating takes the combination of its
                          last ng_every - 1 iterates, summing to one, that minimises the same
@@ -97,9 +98,8 @@ typedef struct {
     int stage_nodes;  /* ray nodes a formal-solve wave stages in LDS at a time, 2..64 (0 = by
                          rule: the most that keep the register budget's occupancy).  0 */
     int tile_points;  /* formal-solve work items (point, line block) a workgroup takes at a time,
-                         1..16 (0 = 1): the grid launch gives each workgroup that many
-                         consecutive items, the persistent launch takes that many from the
-                         queue per atomic.  Results do not depend on it.  0 */
+                         1..16 (0 = 1), consecutive in the launch's order.  Results do not
+                         depend on it.  0 */
 } nlte_params;
 
 /* Defaults listed above; max_iter 50, tol 1e-4, use_alo 1, precision FP64, profile 0, ng_every 0,
@@ -233,7 +233,7 @@ nlte_status nlte_trace_stats(nlte_ctx *ctx, int64_t *total_cells, int *max_len,
 /* Work per origin point as the trace counts it (Sec. 3.2 walks with the velocity
  * sub-steps of Sec. 3.2.1): for each point, the sum over its rays of the ray's elimination
  * steps for one frequency of one line (one per cached cell, or that cell's number of
- * sub-steps) plus one.  cost [P] (host).  The persistent formal solve hands out points in
+ * sub-steps) plus one.  cost [P] (host).  The formal solve with persistent = 1 takes points in
  * decreasing order of this cost. */
 nlte_status nlte_get_point_cost(nlte_ctx *ctx, int64_t *cost);
 
@@ -411,7 +411,7 @@ nlte_status nlte_get_launch(nlte_ctx *ctx, int *lines_per_lane, int *waves_per_s
  * Time formal-solve launch choices on the current model with LTE populations and keep the
  * fastest in the context's parameters: starting from the rule's choice, one dimension at
  * a time (lines per lane, register budget of 1, 2 or 3 waves per SIMD, long or short
- * segments, nodes staged per round, grid or persistent work queue), each candidate timed
+ * segments, nodes staged per round, index or cost order), each candidate timed
  * over `trials` launches after one warm-up (median), the best of each dimension kept
  * before the next.
  * cache_path (nullable): text file of earlier choices keyed by device, library build,

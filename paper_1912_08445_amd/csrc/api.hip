@@ -57,10 +57,9 @@ void dfree(T *&p)
 }
 
 // Scratch of the allocation-free formal solve (nlte_formal_solve_noalloc_dev): the
-// work-queue counter (first kScratchHead bytes) and the line-coefficient staging, in the
-// code object's global memory, one copy per device, alive until the process ends.  Host
-// code never names the array after set-up: it uses the device address that
-// hipGetSymbolAddress returned for that device (scratch_ptr).
+// line-coefficient staging (after kScratchHead bytes) in the code object's global memory, one
+// copy per device, alive until the process ends.  Host code never names the array after
+// set-up: it uses the device address that hipGetSymbolAddress returned for that device.
 constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr size_t kScratchHead = 256;
 // The per-point bounds of the far-wing test follow the staging: 8 bytes per point, for as many
@@ -199,6 +198,34 @@ void set_launch_shape(nlte_ctx *c, SolveArgs &a, bool fp32)
     a.tile = (c->cfg.tile >= 1 && c->cfg.tile <= 16) ? c->cfg.tile : 1;
 }
 
+// Per-pair sums of a split launch are kept to this much.
+constexpr size_t kPartBytes = size_t(64) << 20;
+
+size_t part_need(const SolveArgs &a, bool fp32)
+{
+    return (size_t)a.P * a.groups * a.n_pairs * a.fchunks * 3 * a.lines_per_wave * (fp32 ? sizeof(float) : sizeof(double));
+}
+
+// Waves that share a point's ray pairs: where the points alone would fill the chip's wave
+// slots fewer than eight times, the pairs are split to make up that many work items (at most
+// one pair each).  Below one filling a wave's chain of dependent loads and steps sets the time,
+// up to a few the last, partly filled round does.  Measured, one iteration without / with:
+// sphere of 1,000 points (0.3 fillings) 65 / 42 us; outflows of 600 (0.2) 705 / 206 us, 3,000
+// (1.0) 1058 / 748, 10,000 (3.3) 667 / 632; discs of 1,000 (0.5) 5.70 / 3.21 ms, 5,000 (2.4)
+// 3.98 / 3.81, 10,000 with six pairs (4.9) 1.87 / 1.90; more items than that cost as much as
+// they bring (16 fillings: outflows 658 and 762 us of 632 and 748).
+void set_split(nlte_ctx *c, SolveArgs &a, bool fp32)
+{
+    a.split = 1;
+    a.part = nullptr;
+    const int64_t items = a.P * a.groups, want = (int64_t)c->n_cu * 4 * a.waves * 8;
+    if (c->d_part && a.persistent && items < want && part_need(a, fp32) <= c->part_bytes) {
+        a.split = (int)std::min<int64_t>((want + items - 1) / items, a.n_pairs);
+        a.part = c->d_part;
+    }
+    a.n_blocks = items * a.split;
+}
+
 SolveArgs solve_args(nlte_ctx *c, double *J, double *Jeff, double *L)
 {
     SolveArgs a{};
@@ -236,14 +263,13 @@ SolveArgs solve_args(nlte_ctx *c, double *J, double *Jeff, double *L)
     a.lines_per_wave = ngrp * lpl;
     a.groups = (c->n_lines + a.lines_per_wave - 1) / a.lines_per_wave;
     set_launch_shape(c, a, c->params.precision == NLTE_PREC_FP32_BULK);
-    a.n_blocks = c->P * a.groups;
+    set_split(c, a, c->params.precision == NLTE_PREC_FP32_BULK);
     a.J = J;
     a.Jeff = Jeff;
     a.L = L;
     a.model_done = nullptr;
     a.model_of = c->d_model_of;
     a.order = c->d_order;
-    a.work_counter = c->d_work_counter;
     return a;
 }
 
@@ -259,12 +285,11 @@ void drop_graphs(nlte_ctx *c)
 
 // Line coefficients and the formal solve.  ali: skip points of converged models.
 // capture: enqueue only (no per-kernel event timing, which would synchronise).
-// sc (nullable): caller-provided staging and counter in place of the context's buffers;
-// then nothing is timed, counted or allocated.
+// sc (nullable): caller-provided staging in place of the context's buffers; then nothing is
+// timed, counted or allocated.
 struct FsScratch {
     void *lc;
     float2 *far;
-    unsigned long long *counter;
 };
 
 nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, double *d_Jeff,
@@ -273,7 +298,7 @@ nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, do
 {
     const int fp32 = c->params.precision == NLTE_PREC_FP32_BULK;
     void *lcbuf = sc ? sc->lc : c->d_lc;
-    int64_t *maser = sc ? nullptr : c->d_maser;
+    int64_t *maser = ali ? c->d_maser : nullptr;   // inverted lines are reported by the ALI only
     float2 *far = sc ? sc->far : c->d_far;
     auto lc = [&] { return launch_line_coef(c->sp, c->d_cell, d_pops, c->P, fp32, lcbuf, maser, c->d_ibdy, far, s); };
     HIPCHK(c, capture ? lc() : timed(c, c->st_line_coef, s, lc));
@@ -281,12 +306,12 @@ nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, do
     if (sc) {
         a.lc = sc->lc;
         a.far = sc->far;
-        a.work_counter = sc->counter;
+        a.split = 1;   // (the context's per-pair sums are not part of the fixed scratch)
+        a.n_blocks = a.P * a.groups;
         a.exec_steps = nullptr;
     }
     if (ali) a.model_done = c->d_model_done;
-    if (a.persistent) HIPCHK(c, launch_fill_u64(a.work_counter, 1, 0ull, s));
-    auto fs = [&] { return launch_formal_solve(a, c->cfg, fp32, s); };
+    auto fs = [&] { return launch_formal_solve(a, fp32, s); };
     HIPCHK(c, capture ? fs() : timed(c, c->st_formal, s, fs));
     return NLTE_OK;
 }
@@ -592,8 +617,9 @@ nlte_status formal_solve_band_impl(nlte_ctx *c, const double *d_pops, double *d_
     if (a.lines_per_wave / a.ngrp > 2) {   // the band kernel takes one or two lines per lane
         a.lines_per_wave = a.ngrp * 2;
         a.groups = (c->n_lines + a.lines_per_wave - 1) / a.lines_per_wave;
-        a.n_blocks = c->P * a.groups;
     }
+    a.split = 1;
+    a.n_blocks = c->P * a.groups;
     {   // its own launch: FP64, a budget of two waves per SIMD, the same segment mode
         const SolveConfig keep = c->cfg;
         c->cfg.waves = 2;
@@ -775,7 +801,7 @@ nlte_status need_scat(nlte_ctx *c)
 nlte_status formal_solve_scat_impl(nlte_ctx *c, const double *d_pops, const double *d_jin, double *d_J,
                                    double *d_Jeff, double *d_L, double *d_jout, hipStream_t s, bool ali)
 {
-    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, nullptr, nullptr, s));
+    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, ali ? c->d_maser : nullptr, nullptr, nullptr, s));
     ScatArgs a{};
     a.cell = c->d_cell;
     a.lc = c->d_lc;
@@ -887,7 +913,6 @@ nlte_status nlte_create(nlte_ctx **out, int hip_device)
         hipHostMalloc((void **)&c->h_conv, sizeof(ConvResult) * 1025, 0) != hipSuccess ||
         hipMalloc((void **)&c->d_active, sizeof(int32_t)) != hipSuccess ||
         hipHostMalloc((void **)&c->h_active, sizeof(int32_t), 0) != hipSuccess ||
-        hipMalloc((void **)&c->d_work_counter, sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc((void **)&c->d_exec, sizeof(unsigned long long)) != hipSuccess ||
         hipMemset(c->d_exec, 0, sizeof(unsigned long long)) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
@@ -901,7 +926,6 @@ nlte_status nlte_create(nlte_ctx **out, int hip_device)
         c->device_name = prop.gcnArchName;
     }
     if (c->n_cu <= 0) c->n_cu = 256;
-    c->cfg.n_wg = c->n_cu * 16;
     *out = c;
     return NLTE_OK;
 }
@@ -930,6 +954,7 @@ void nlte_destroy(nlte_ctx *c)
     dfree(c->d_rcells);
     dfree(c->d_lc);
     dfree(c->d_far);
+    dfree(c->d_part);
     dfree(c->d_pops_a);
     dfree(c->d_pops_b);
     dfree(c->d_J);
@@ -940,7 +965,6 @@ void nlte_destroy(nlte_ctx *c)
     dfree(c->d_conv);
     dfree(c->d_maser);
     dfree(c->d_active);
-    dfree(c->d_work_counter);
     dfree(c->d_order);
     dfree(c->d_cost);
     dfree(c->d_model_of);
@@ -1451,6 +1475,17 @@ nlte_status nlte_trace(nlte_ctx *c)
     auto t1 = std::chrono::steady_clock::now();
     c->st_trace.ms += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st_trace.launches += 1;
+    {   // room for the per-pair sums of split launches, where there are few enough points
+        const size_t need_bytes = sizeof(double) * (size_t)c->P * c->n_pairs * 3 * (c->n_lines + 2 * kMaxLpl) *
+                                  (c->n_q <= kWave ? 1 : (c->n_q + kWave - 1) / kWave);
+        if (need_bytes <= kPartBytes) {
+            if ((st = dalloc(c, (char **)&c->d_part, need_bytes))) return st;
+            c->part_bytes = need_bytes;
+        } else {
+            dfree(c->d_part);
+            c->part_bytes = 0;
+        }
+    }
     c->total_cells = total;
     c->max_len = (int)h_sums[0];
     c->total_steps = (int64_t)h_sums[1] - n;
@@ -1551,8 +1586,6 @@ nlte_status nlte_formal_solve_dev(nlte_ctx *c, const double *d_pops, double *d_J
     if (!d_pops || !d_J || !d_Jeff || !d_L) return fail(c, NLTE_E_INVALID_ARG, "null buffer");
     (void)hipSetDevice(c->device);
     hipStream_t s = pick(c, stream);
-    // a fill kernel, not a memset node: callers may capture this stream in a graph
-    HIPCHK(c, launch_fill_u64(reinterpret_cast<unsigned long long *>(c->d_maser), 1, 0ull, s));
     return formal_solve_impl(c, d_pops, d_J, d_Jeff, d_L, s);
 }
 
@@ -1577,7 +1610,7 @@ nlte_status nlte_formal_solve_noalloc_dev(nlte_ctx *c, const double *d_pops, dou
     (void)hipSetDevice(c->device);
     hipStream_t s = pick(c, stream);
     unsigned char *b8 = static_cast<unsigned char *>(base);
-    FsScratch sc{b8 + kScratchHead, reinterpret_cast<float2 *>(b8 + kScratchBytes), static_cast<unsigned long long *>(base)};
+    FsScratch sc{b8 + kScratchHead, reinterpret_cast<float2 *>(b8 + kScratchBytes)};
     // enqueue only: no event timing (which would synchronise), no step counting
     return formal_solve_impl(c, d_pops, d_J, d_Jeff, d_L, s, false, true, &sc);
 }
@@ -2334,7 +2367,6 @@ nlte_status nlte_formal_solve_scat_dev(nlte_ctx *c, const double *d_pops, const 
     if (d_jnu_in == d_jnu_out) return fail(c, NLTE_E_INVALID_ARG, "jnu_in and jnu_out must differ");
     (void)hipSetDevice(c->device);
     hipStream_t s = pick(c, stream);
-    HIPCHK(c, launch_fill_u64(reinterpret_cast<unsigned long long *>(c->d_maser), 1, 0ull, s));
     return formal_solve_scat_impl(c, d_pops, d_jnu_in, d_J, d_Jeff, d_L, d_jnu_out, s, false);
 }
 
@@ -2450,7 +2482,7 @@ nlte_status nlte_image_dev(nlte_ctx *c, const double *d_pops, int ray, int line,
     }
     HIPCHK(c, hipMemcpyAsync(c->d_vch, v_ch, sizeof(double) * n_ch, hipMemcpyHostToDevice, s));
     // FP64 line coefficients of these populations
-    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, c->d_maser, nullptr, nullptr, s));
+    HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, nullptr, nullptr, nullptr, s));
     const double nu = c->nu[line];
     ImageArgs a{};
     a.cell = c->d_cell;

@@ -108,10 +108,10 @@ hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const dou
 
 // The kernels are templates in formal_solve_kernels.h, instantiated per precision in
 // fs_fp64.hip and fs_fp32.hip (compiled in parallel).
-hipError_t launch_formal_solve(const SolveArgs &a, const SolveConfig &cfg, int fp32, hipStream_t s)
+hipError_t launch_formal_solve(const SolveArgs &a, int fp32, hipStream_t s)
 {
     if (a.n_blocks == 0) return hipSuccess;
-    return fp32 ? launch_formal_solve_f32(a, cfg, s) : launch_formal_solve_f64(a, cfg, s);
+    return fp32 ? launch_formal_solve_f32(a, s) : launch_formal_solve_f64(a, s);
 }
 
 }  // namespace nlte

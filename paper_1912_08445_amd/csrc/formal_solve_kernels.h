@@ -13,6 +13,8 @@
 // projection, Doppler coefficients, sub-step count and increments, kappa and S of its
 // lines); the sweep reads them as broadcasts.
 #pragma once
+#include <algorithm>
+
 #include "device_math.h"
 #include "nlte_internal.h"
 
@@ -663,8 +665,9 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename 
     }
 }
 
-// All (line, frequency) work of one wave for origin point O and line block w, accumulated
-// over every ray pair and written to J, L*, Jeff.  Points of models that already
+// All (line, frequency) work of one wave for origin point O and line block w over ray pairs
+// p_beg .. p_end - 1, accumulated over them and written to J, L*, Jeff (or, where the point's
+// pairs are split over several waves, left per pair in a.part).  Points of models that already
 // converged are skipped (their outputs are not needed).
 // Lanes: with two groups, group g takes lanes 32 g .. 32 g + n_q - 1 (one frequency each)
 // and lines line0 + g LPL ...; with one group, lanes 0..63 take frequencies c 64 + lane of
@@ -675,7 +678,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename 
 // there, and lane q LPL + l of each group sums row (q, l) over the group's frequencies in
 // index order and adds it to its one accumulator (one register, not three per line).
 template <bool F32, int LPL, bool COLLAPSE, bool BAND = false>
-__device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
+__device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w, int p_beg, int p_end,
                                            NodeRec<typename Bulk<F32>::T, 2 * LPL> *rec,
                                            double (*red)[LPL][kWave], const double *tab)
 {
@@ -703,7 +706,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
     const int rq = sub / LPL, rl = sub - rq * LPL;   // the row this lane sums
     LineState<T, LPL> ls;
     unsigned long long my_exec = 0;   // executed node-frequency steps of this lane
-    for (int p = 0; p < a.n_pairs; ++p) {
+    for (int p = p_beg; p < p_end; ++p) {
         const int r = a.pair_r[p], rb = a.anti[r];
         for (int c = 0; c < a.fchunks; ++c) {
             const int nidx = (a.fchunks == 1) ? sub : c * kWave + lane;
@@ -777,7 +780,13 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
             if (sub < 3 * LPL) {
                 Acc sum = 0;
                 for (int i = 0; i < nfq; ++i) sum += (Acc)red[rq][rl][col0 + i];
-                acc += sum;
+                if (!BAND && a.split > 1) {
+                    // another wave has the point's other pairs: k_pair_sums adds them in order
+                    const int64_t row = ((O * a.groups + w) * a.n_pairs + p) * a.fchunks + c;
+                    static_cast<Acc *>(a.part)[(row * ngrp + grp) * (3 * LPL) + sub] = sum;
+                } else {
+                    acc += sum;
+                }
             }
             if (BAND) {
                 __syncthreads();
@@ -821,6 +830,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
         for (int o = kWave / 2; o > 0; o >>= 1) my_exec += __shfl_xor(my_exec, o);
         if (lane == 0) atomicAdd(a.exec_steps, my_exec);
     }
+    if (!BAND && a.split > 1) return;
     if (sub < (BAND ? 5 : 3) * LPL && rl < LPL) {
         const int q = sub / LPL, l = sub - q * LPL, li = grp * LPL + l;
         if (li < nlw) {
@@ -844,13 +854,17 @@ constexpr size_t fs_lds_bytes(int ns)
     return fs_rows_bytes<F32, LPL>() + (size_t)ns * sizeof(NodeRec<typename Bulk<F32>::T, 2 * LPL>);
 }
 
-// Work items are (point, line block); a workgroup takes a.tile consecutive items at a time.
-// Grid form: one workgroup per tile of items; consecutive hardware workgroups go
-// round-robin to the 8 XCDs and each XCD gets a contiguous range of origin points, so
-// that the cells their rays share stay in that XCD's L2.  Persistent form (a.persistent):
-// a fixed grid of workgroups takes tiles from an atomic counter in the order a.order gives
-// (points by decreasing cached step count, so the longest items start first and the tail
-// is short); every workgroup leaves the loop once the counter has passed the last item.
+// Work items are (point, line block), or with a.split > 1 the split parts of its ray pairs; a
+// workgroup takes a.tile consecutive items.  Grid form: points in index order, consecutive
+// hardware workgroups go round-robin to the 8 XCDs and each XCD gets a contiguous range of
+// origin points, so that the cells their rays share stay in that XCD's L2.  Ordered form
+// (a.persistent): points in the order a.order gives (by decreasing cached step count), one
+// tile after the next in the order of the workgroups, which the hardware starts as room comes
+// free: the longest items start first and the tail is short.  (A fixed grid of workgroups that
+// took their items from an atomic counter did the same at a few ns per item and a launch to
+// clear the counter: spheres of 12,000 and 60,000 points 413 and 2402 us against 363 and 2340,
+// the outflow of 20,011 points 4.94 ms against 4.75, FP32 3.61 against 3.47; only five FP64
+// lines per lane, whose workgroups also set up spill space, gained 1% from it.)
 // W: waves per SIMD the register budget is built for.
 template <bool F32, int LPL, int W, bool COLLAPSE>
 __global__ __launch_bounds__(64, W) void k_formal_solve(SolveArgs a)
@@ -863,68 +877,91 @@ __global__ __launch_bounds__(64, W) void k_formal_solve(SolveArgs a)
         if (threadIdx.x < 16) tab[threadIdx.x] = kExp2Sixteenths[threadIdx.x];
         __syncthreads();
     }
-    // one call site for both forms (the sweep is compiled once): a grid workgroup takes
-    // its own item and stops
-    // a workgroup takes a.tile consecutive items at a time
-    __shared__ unsigned long long item_s;
+    // (one call site for both forms: the sweep is compiled once)
     const int64_t tile = a.tile;
-    int64_t first;
-    if (a.persistent) {
-        if (threadIdx.x == 0) item_s = atomicAdd(a.work_counter, (unsigned long long)tile);
-        __syncthreads();
-        first = (int64_t)item_s;
-    } else {
-        const int64_t n_tiles = (a.n_blocks + tile - 1) / tile;
-        const int64_t nb8 = (n_tiles + 7) / 8;
-        first = ((int64_t)(blockIdx.x & 7) * nb8 + (blockIdx.x >> 3)) * tile;
-    }
-    while (first < a.n_blocks) {
+    const int64_t n_tiles = (a.n_blocks + tile - 1) / tile;
+    const int64_t nb8 = (n_tiles + 7) / 8, n_points = a.n_blocks / a.split;   // (times line blocks)
+    for (int64_t v = blockIdx.x; v < nb8 * 8; v += gridDim.x) {   // (gridDim.x is a multiple of 8)
+        const int64_t first = (a.persistent ? v : (v & 7) * nb8 + (v >> 3)) * tile;
         const int64_t last = first + tile < a.n_blocks ? first + tile : a.n_blocks;
         for (int64_t item = first; item < last; ++item) {
-            const int64_t rank = item / a.groups;
+            // part by part: consecutive workgroups, which go to the XCDs in turn, have different
+            // points and like costs (the parts of a point side by side gave an XCD the same part
+            // of every point where 8 is a multiple of their number: up to twice the time)
+            const int part = (int)(item / n_points);
+            const int64_t block = item - part * n_points;
+            const int64_t rank = block / a.groups;
             const int64_t O = a.persistent ? (int64_t)a.order[rank] : rank;
-            solve_item<F32, LPL, COLLAPSE>(a, O, (int)(item - rank * a.groups), rec, red, tab);
+            solve_item<F32, LPL, COLLAPSE>(a, O, (int)(block - rank * a.groups), part * a.n_pairs / a.split,
+                                           (part + 1) * a.n_pairs / a.split, rec, red, tab);
         }
-        if (!a.persistent) break;
-        __syncthreads();
-        if (threadIdx.x == 0) item_s = atomicAdd(a.work_counter, (unsigned long long)tile);
-        __syncthreads();
-        first = (int64_t)item_s;
     }
 }
 
+// J, L* and Jeff from the per-pair sums of a split launch, added in the order in which one
+// wave would have met the pairs (the same bits).  One thread per (point, line block, lane
+// group, sum).
+template <bool F32, int LPL>
+__global__ __launch_bounds__(256) void k_pair_sums(SolveArgs a)
+{
+    using Acc = typename Bulk<F32>::T;
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int slots = a.ngrp * 3 * LPL;
+    if (t >= a.P * a.groups * slots) return;
+    const int64_t block = t / slots;
+    const int slot = (int)(t - block * slots);
+    const int64_t O = block / a.groups;
+    const int w = (int)(block - O * a.groups);
+    if (a.model_done != nullptr && a.model_done[a.model_of[O]]) return;
+    const int grp = slot / (3 * LPL), q = (slot - grp * 3 * LPL) / LPL;
+    const int li = grp * LPL + (slot - grp * 3 * LPL - q * LPL);
+    const int line = w * a.lines_per_wave + li;
+    if (li >= a.lines_per_wave || line >= a.n_lines) return;
+    const int rows = a.n_pairs * a.fchunks;
+    const Acc *part = static_cast<const Acc *>(a.part) + block * rows * slots + slot;
+    Acc acc = 0;
+#pragma unroll 8
+    for (int i = 0; i < rows; ++i) acc += part[(int64_t)i * slots];
+    (q == 0 ? a.J : q == 1 ? a.L : a.Jeff)[O * a.n_lines + line] = a.norm * (double)acc;
+}
+
 template <bool F32, int LPL, int W, bool COLLAPSE>
-hipError_t launch_fs_variant(const SolveArgs &a, int n_wg, hipStream_t s)
+hipError_t launch_fs_variant(const SolveArgs &a, hipStream_t s)
 {
     const size_t lds = fs_lds_bytes<F32, LPL>(a.ns);
     const int64_t n_tiles = (a.n_blocks + a.tile - 1) / a.tile;
-    const unsigned grid = a.persistent ? (unsigned)n_wg : (unsigned)(((n_tiles + 7) / 8) * 8);
+    // one workgroup per tile (bounded: a launch counts its threads in 32 bits)
+    const unsigned grid = (unsigned)(std::min<int64_t>((n_tiles + 7) / 8, 1 << 22) * 8);
     hipLaunchKernelGGL((k_formal_solve<F32, LPL, W, COLLAPSE>), dim3(grid), dim3(kWave), lds, s, a);
+    if (a.split > 1) {
+        const int64_t n = a.P * a.groups * a.ngrp * 3 * LPL;
+        hipLaunchKernelGGL((k_pair_sums<F32, LPL>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
 template <bool F32, int LPL>
-hipError_t launch_fs_lpl(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s)
+hipError_t launch_fs_lpl(const SolveArgs &a, hipStream_t s)
 {
     if (a.waves == 3)
-        return a.collapse ? launch_fs_variant<F32, LPL, 3, true>(a, cfg.n_wg, s)
-                          : launch_fs_variant<F32, LPL, 3, false>(a, cfg.n_wg, s);
+        return a.collapse ? launch_fs_variant<F32, LPL, 3, true>(a, s)
+                          : launch_fs_variant<F32, LPL, 3, false>(a, s);
     if (a.waves == 1)
-        return a.collapse ? launch_fs_variant<F32, LPL, 1, true>(a, cfg.n_wg, s)
-                          : launch_fs_variant<F32, LPL, 1, false>(a, cfg.n_wg, s);
-    return a.collapse ? launch_fs_variant<F32, LPL, 2, true>(a, cfg.n_wg, s)
-                      : launch_fs_variant<F32, LPL, 2, false>(a, cfg.n_wg, s);
+        return a.collapse ? launch_fs_variant<F32, LPL, 1, true>(a, s)
+                          : launch_fs_variant<F32, LPL, 1, false>(a, s);
+    return a.collapse ? launch_fs_variant<F32, LPL, 2, true>(a, s)
+                      : launch_fs_variant<F32, LPL, 2, false>(a, s);
 }
 
 template <bool F32>
-hipError_t launch_fs_prec(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s)
+hipError_t launch_fs_prec(const SolveArgs &a, hipStream_t s)
 {
     switch (a.lines_per_wave / a.ngrp) {
-    case 1: return launch_fs_lpl<F32, 1>(a, cfg, s);
-    case 2: return launch_fs_lpl<F32, 2>(a, cfg, s);
-    case 3: return launch_fs_lpl<F32, 3>(a, cfg, s);
-    case 4: return launch_fs_lpl<F32, 4>(a, cfg, s);
-    case 5: return launch_fs_lpl<F32, 5>(a, cfg, s);
+    case 1: return launch_fs_lpl<F32, 1>(a, s);
+    case 2: return launch_fs_lpl<F32, 2>(a, s);
+    case 3: return launch_fs_lpl<F32, 3>(a, s);
+    case 4: return launch_fs_lpl<F32, 4>(a, s);
+    case 5: return launch_fs_lpl<F32, 5>(a, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -4,9 +4,9 @@
 
 namespace nlte {
 
-hipError_t launch_formal_solve_f32(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s)
+hipError_t launch_formal_solve_f32(const SolveArgs &a, hipStream_t s)
 {
-    return launch_fs_prec<true>(a, cfg, s);
+    return launch_fs_prec<true>(a, s);
 }
 
 size_t formal_solve_lds_f32(int lpl, int ns)

@@ -4,9 +4,9 @@
 
 namespace nlte {
 
-hipError_t launch_formal_solve_f64(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s)
+hipError_t launch_formal_solve_f64(const SolveArgs &a, hipStream_t s)
 {
-    return launch_fs_prec<false>(a, cfg, s);
+    return launch_fs_prec<false>(a, s);
 }
 
 size_t formal_solve_lds_f64(int lpl, int ns)
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64, 2) void k_formal_solve_band(SolveArgs a)
     const int64_t lb = (int64_t)(blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);
     if (lb >= a.n_blocks) return;
     const int64_t O = lb / a.groups;
-    solve_item<false, LPL, LONG, true>(a, O, (int)(lb - O * a.groups), rec, red, tab);
+    solve_item<false, LPL, LONG, true>(a, O, (int)(lb - O * a.groups), 0, a.n_pairs, rec, red, tab);
 }
 
 hipError_t launch_formal_solve_band(const SolveArgs &a, hipStream_t s)

@@ -82,18 +82,19 @@ struct SolveArgs {
     int ns;                  // ray nodes a wave stages in LDS per round (2..64)
     int waves;               // register budget of the launch: 2 or 3 waves per SIMD
     int collapse;            // 1: long-segment mode (profile recurrence)
-    int persistent;          // 1: items from the work counter in decreasing-cost order
+    int persistent;          // 1: workgroups take items in decreasing-cost order
     int tile;                // work items a workgroup takes at a time (1..16)
-    int64_t n_blocks;        // work items (P * groups)
+    int split;               // waves that share a point's ray pairs (1: none)
+    void *part;              // split: per-pair sums [P][groups][n_pairs][fchunks][ngrp][3 * lpl]
+    int64_t n_blocks;        // work items (P * groups * split)
     double *J, *Jeff, *L;    // [P][n_lines]
     double *Jb, *Ld;         // band operator: J without the band's share, its diagonal [P][n_lines]
     double *Ln;              // band operator: coupling to the first cell per ray [P][n_lines][n_rays]
     // ALI only: points of converged models are skipped (null: solve every point)
     const uint8_t *model_done;
     const int32_t *model_of;
-    // persistent form: item order (points by decreasing cost) and the work counter
+    // ordered form: points by decreasing cost
     const int32_t *order;
-    unsigned long long *work_counter;
     // profile mode: executed node-frequency elimination steps (null: not counted)
     unsigned long long *exec_steps;
 };
@@ -175,9 +176,8 @@ struct SolveConfig {
     int waves = 0;            // register budget for 2 or 3 waves per SIMD (0 = by rule)
     int long_seg = -1;        // long-segment mode: 1 on, 0 off, -1 by the trace's steps per cell
     int ns = 0;               // ray nodes staged per round (2..64; 0 = by rule)
-    int persistent = 0;       // 1: work-queue kernel in decreasing-cost order
+    int persistent = 0;       // 1: points in decreasing-cost order
     int tile = 0;             // work items per workgroup grab (1..16; 0 = 1)
-    int n_wg = 0;             // workgroups of the persistent kernel
 };
 
 struct KernelStat {
@@ -277,7 +277,6 @@ struct nlte_ctx {
     // ray cache, per-point costs and the decreasing-cost order
     int32_t *d_order = nullptr;                 // [P]
     unsigned long long *d_cost = nullptr;       // [P] elimination steps per frequency
-    unsigned long long *d_work_counter = nullptr;
     unsigned long long *d_exec = nullptr;   // executed formal-solve steps (profile mode)
     bool traced = false;
     int64_t *d_roff = nullptr;
@@ -289,6 +288,8 @@ struct nlte_ctx {
     // work buffers (sized for P)
     void *d_lc = nullptr;  // line coefficients
     float2 *d_far = nullptr;  // [P] bounds of the far-wing test
+    void *d_part = nullptr;   // per-pair sums of split formal solves (sized by the trace)
+    size_t part_bytes = 0;
     double *d_pops_a = nullptr, *d_pops_b = nullptr;
     double *d_J = nullptr, *d_Jeff = nullptr, *d_L = nullptr;
     uint8_t *d_flags = nullptr;
@@ -403,9 +404,9 @@ hipError_t scan_lengths(int64_t *len_then_off, int64_t n, void *tmp, size_t *tmp
 hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops,
                             int64_t P, int fp32, void *lc, int64_t *maser_count, const double *ibdy, float2 *far,
                             hipStream_t s);
-hipError_t launch_formal_solve(const SolveArgs &a, const SolveConfig &cfg, int fp32, hipStream_t s);
-hipError_t launch_formal_solve_f64(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s);
-hipError_t launch_formal_solve_f32(const SolveArgs &a, const SolveConfig &cfg, hipStream_t s);
+hipError_t launch_formal_solve(const SolveArgs &a, int fp32, hipStream_t s);
+hipError_t launch_formal_solve_f64(const SolveArgs &a, hipStream_t s);
+hipError_t launch_formal_solve_f32(const SolveArgs &a, hipStream_t s);
 // dynamic LDS bytes of one formal-solve workgroup with lpl lines per lane and ns staged nodes
 size_t formal_solve_lds_f64(int lpl, int ns);
 size_t formal_solve_lds_f32(int lpl, int ns);
