@@ -167,18 +167,17 @@ void set_launch_shape(nlte_ctx *c, SolveArgs &a, bool fp32)
 {
     const int lpl = a.lines_per_wave / a.ngrp;
     // by rule: 3 waves per SIMD in FP32 and up to two lines per lane in FP64, else 2
-    // (measured on the disc: the whole register file for one wave removes the spills of
-    // five FP64 lines per lane but leaves too little to hide latency; five FP64 lines at
-    // three waves spill inside the node loops; five FP32 lines fit three waves with a few
-    // spills outside them, and the third wave takes the disc's FP32 sweep from 4.0 to 3.5 s)
+    // (measured at five lines per lane, 2 waves / 3: the FP64 disc of 30,011 points 77 / 100 ms,
+    // the third wave's registers spill inside the node loops; the FP32 disc of 24,000 points 48.8 /
+    // 45.1 ms, a few spills outside them)
     a.waves = (c->cfg.waves >= 1 && c->cfg.waves <= 3) ? c->cfg.waves : ((lpl <= 2 || fp32) ? 3 : 2);
     // long-segment mode (the profile by recurrence within a segment) where sub-step segments
-    // are long on average and a lane holds at most three lines.  Measured short / long on an
-    // outflow of 20,011 points, two lines per lane, against its elimination steps per cell:
-    // FP64 6.08 / 6.24 ms at 3.1, 6.40 / 5.53 at 5.0, 6.63 / 4.79 at 13; FP32 3.72 / 3.78 at
-    // 1.6, 3.89 / 3.46 at 3.1.  Five lines per lane: the recurrence's state spills in FP64
-    // (the disc of 30,011 points at 2.2: 95 / 155 ms; an outflow with nine lines at 16.6:
-    // 6.1 / 7.5) and gains nothing in FP32 (4.38 / 4.35 there, the disc 50.9 / 52.1).
+    // are long on average and a lane holds at most three lines.  Measured short / long on
+    // outflows against their elimination steps per cell, two lines per lane and 20,011 points:
+    // FP64 5.87 / 5.57 ms at 1.6, 5.87 / 5.46 at 3.1, 5.80 / 4.96 at 5.0, 6.15 / 4.43 at 13 (one line per lane: 3.94 /
+    // 4.48 at 1.9, 4.34 / 4.21 at 3.8); FP32 3.89 / 4.03 at 1.6, 3.95 / 3.69 at 3.1.  Five lines
+    // per lane: the recurrence's state spills in FP64 (10,011 points, nine lines: 4.25 / 6.67 at
+    // 1.9, 5.93 / 6.24 at 17), and in FP32 the modes are one kernel.
     const double per_cell = c->total_cells > 0 ? (double)c->total_steps / (double)c->total_cells : 0.0;
     a.collapse = c->cfg.long_seg >= 0 ? c->cfg.long_seg : (lpl <= 3 && per_cell > (fp32 ? 2.0 : 3.5) ? 1 : 0);
     // the most staged nodes whose LDS keeps the register budget's occupancy (160 KiB per CU):

@@ -16,7 +16,7 @@
 // with Q = 1, y = I_boundary, D_- = 0 before the first node, which is exactly the Auer
 // boundary row.  No step divides by an optical depth.  The sweep carries Q and y as
 // fractions N/D and Y/D (scaled by sqrt 2, which cancels at O), which turns each step
-// into three multiply-adds of non-negative numbers with no division (see elim_step).
+// into three multiply-adds of non-negative numbers with no division (see elim_p).
 // At O the two halves combine into
 //   u_O = (h_O S_O + y_f + y_b) / (h_O + Q_f + Q_b),   Lambda_OO = h_O / (h_O + Q_f + Q_b),
 // and u_O - Lambda_OO S_O = (y_f + y_b) / (h_O + Q_f + Q_b) without cancellation.

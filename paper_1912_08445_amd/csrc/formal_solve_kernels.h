@@ -9,11 +9,12 @@
 // the LPL lines of a lane share its profile evaluation and its recurrence; with up to
 // five lines per lane a point's nine lines take a single wave, which stages each ray
 // segment and evaluates each profile once.  All lanes walk the same nodes (uniform control
-// flow).  The wave stages `ns` nodes of a ray at a time in LDS (position, velocity
-// projection, Doppler coefficients, sub-step count and increments, kappa and S of its
-// lines); the sweep reads them as broadcasts.
+// flow).  The wave stages `ns` nodes of a ray at a time in LDS (Doppler coefficients, the
+// length of their segment's sub-steps, kappa and S of its lines; see Node), the sub-step
+// counts and what a segment needs of the wave as a whole in scalar registers.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "device_math.h"
 #include "nlte_internal.h"
@@ -22,9 +23,8 @@ namespace nlte {
 
 constexpr double kSqrt2 = 1.41421356237309504880;
 constexpr double kInv2Sqrt2 = 0.35355339059327376220;  // 1 / (2 sqrt 2)
-// The elimination state only grows (see elim_step); it is rescaled by a power of two once
-// any line's D passes 2^300, checked after every node (every second node in the short
-// mode's segment loop) and at least every fourth sub-step, which leaves room for steps
+// The elimination state only grows (see elim_p); it is rescaled by a power of two once
+// any line's D passes 2^300, checked at least every fourth step, which leaves room for steps
 // with D_+ up to about 2^70 before the FP64 range ends.
 // Power-of-two rescaling is exact, so when it happens does not change any result.
 constexpr double kRenormAbove = 2.0370359763344861e90;   // 2^300
@@ -40,45 +40,157 @@ struct Bulk<true> {
     using T2 = float2;
 };
 
-// One staged node of a half ray.  (a, b) give the Doppler offset of a lane's frequency
-// x_q at this node as x = a x_q - b.  The segment to the next node toward O has m
-// sub-intervals of length 2 sqrt(2) dzq; per sub-interval x changes by da x_q - db.  maxdx
-// bounds |dx| over all frequencies, K is the restart interval of the profile recurrence
-// (0: evaluate every profile directly), both for the long-segment mode.  kap, S: line-centre
-// opacity and source function of the wave's lines.
-template <typename T, int NLW>
-struct NodeRec {
-    T a, b, dzq, da, db, inv_m, maxdx;
-    int m, K;
-    T kap[NLW], S[NLW];
+// A staged node of a half ray: one row of Node::kStride values in LDS.
+//   (a, b)  the Doppler offset of a lane's frequency x_q at this node, x = a x_q - b;
+//   the segment to the next node toward O has m sub-intervals (im = 1/m) of length
+//   2 sqrt(2) dzq; per sub-interval x changes by da x_q - db (read by the FP32 form only);
+//   kappa, S: line-centre opacity and source function of each line group's lines.
+// Two ways to read a node (kRowValues chooses; the values and what is done with them are the same):
+//   rows   lane e of every row of 16 lanes loads value e of its line group ([kappa][S] of the
+//          group's lines, then the six values of the node), ONE load and one register per node, and
+//          each value is broadcast over its row by a DPP move where it is used (all lanes of a row
+//          belong to one group).  Between two cells kappa and S are linear, so a velocity sub-node
+//          is the two nodes' values combined by one multiply-add for all lines.
+//   values every lane loads every value (an LDS broadcast) and keeps its lines' in registers.
+// Instruction issue and the number of waves bound the sweep.  Five lines by values kept both
+// nodes' values, their differences and the running values in 80 FP64 registers and took an
+// instruction for each line and sub-node; by rows a disc of 30,011 points and nine lines takes
+// 77 ms (95.6 before), in FP32 one of 24,000 points 45.1 (51.8).  The FP64 long mode gains with two
+// lines too (outflow of 20,011 points 4.42 ms by rows, 4.60 by values, 4.75 before); without
+// the recurrence's registers, or with one line, the moves cost more than they save (a sphere of
+// 30,000 points 1.65 ms by rows, 0.91 by values; that outflow in FP32 4.15 and 3.53).
+template <bool F32, int LPL, bool LONG>
+inline constexpr bool kRowValues = LPL >= 4 || (!F32 && LONG && LPL >= 2);
+
+template <int LPL, bool ROWS>
+struct Node {
+    static constexpr int kCommon = 4 * LPL;              // a, b, dzq, im, da, db
+    // (rows: odd, so that nodes start in different banks when they are written; otherwise
+    // even, so that values are read in aligned pairs)
+    static constexpr int kStride = 4 * LPL + 6 + (ROWS ? 1 : 0);
+};
+
+// The value that lane N of this lane's row of 16 holds.
+extern "C" __device__ __attribute__((const)) long nlte_update_dpp_i64(long, long, int, int, int, bool)
+    __asm("llvm.amdgcn.update.dpp.i64");
+template <int N>
+__device__ __forceinline__ double row_value(double v)
+{
+    return __builtin_bit_cast(double, nlte_update_dpp_i64(0l, __builtin_bit_cast(long, v), 0x150 + N, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float row_value(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + N, 0xF, 0xF, true));
+}
+
+// f(0), f(1), .., f(N - 1) with the argument known when it is compiled (row_value needs that)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unrolled<N, I + 1>(f);
+    }
+}
+
+// The kappa and S of a lane's lines at a node: by rows one value of the node per lane.
+template <typename T, int LPL, bool ROWS>
+struct NodeVals {
+    T v[ROWS ? 1 : 2 * LPL];
+    template <int L>
+    __device__ __forceinline__ T kap() const
+    {
+        if constexpr (ROWS)
+            return row_value<L>(v[0]);
+        else
+            return v[L];
+    }
+    template <int L>
+    __device__ __forceinline__ T src() const
+    {
+        return kap<LPL + L>();
+    }
+    static constexpr int kN = ROWS ? 1 : 2 * LPL;
+};
+
+// The same values in FP64 (rows: one conversion for all lines).
+template <int LPL, bool ROWS, typename T>
+__device__ __forceinline__ NodeVals<double, LPL, ROWS> in_fp64(const NodeVals<T, LPL, ROWS> &v)
+{
+    NodeVals<double, LPL, ROWS> w;
+#pragma unroll
+    for (int k = 0; k < w.kN; ++k) w.v[k] = (double)v.v[k];
+    return w;
+}
+
+// Reads of a staged node: `my` points at this lane's value of node 0 (rows) or at its line
+// group's values there, `com` at the node's own values (not for rows).
+template <typename T, int LPL, bool ROWS>
+struct NodeReader {
+    const T *my, *com;
+    using Vals = NodeVals<T, LPL, ROWS>;
+    typedef T Pair __attribute__((ext_vector_type(2)));
+    __device__ __forceinline__ NodeReader(const T *rec, int grp, int lane)
+    {
+        const int e = lane & 15;
+        my = rec + (!ROWS || e < 2 * LPL ? grp * 2 * LPL : 0);
+        if constexpr (ROWS) my += e < 2 * LPL ? e : Node<LPL, ROWS>::kCommon + min(e - 2 * LPL, 5);
+        com = rec + Node<LPL, ROWS>::kCommon;
+    }
+    __device__ __forceinline__ Vals values(int i) const
+    {
+        Vals w;
+        if constexpr (ROWS) {
+            w.v[0] = my[i * Node<LPL, ROWS>::kStride];
+        } else {
+#pragma unroll
+            for (int k = 0; k < Vals::kN; k += 2) {
+                const Pair p = *reinterpret_cast<const Pair *>(my + i * Node<LPL, ROWS>::kStride + k);
+                w.v[k] = p.x;
+                w.v[k + 1] = p.y;
+            }
+        }
+        return w;
+    }
+    // value K of the node itself (0 a, 1 b, 2 dzq, 3 im, 4 da, 5 db), whose row values are in w
+    template <int K>
+    __device__ __forceinline__ T own(int i, const Vals &w) const
+    {
+        if constexpr (ROWS)
+            return row_value<2 * LPL + K>(w.v[0]);
+        else
+            return (*reinterpret_cast<const Pair *>(com + i * Node<LPL, ROWS>::kStride + (K & ~1)))[K & 1];
+    }
 };
 
 // Elimination state of a half sweep in homogeneous form: the Rybicki-Hummer quantities
 // Q = N / (sqrt 2 D) and y = Y / (sqrt 2 D), and Hm = D_- / sqrt 2, the previous
-// optical-depth step (see elim_step).
+// optical-depth step (see elim_p).
 struct HalfState {
     double N, D, Y, Hm;
     double hd;   // weight h d of the last step (rescaled with the state): the share of the
     double Sl;   // last eliminated node's source Sl in Y (read by the band operator only)
 };
 
-// e^{-x^2}: FP64 by the table-driven exponential (tab: 2^{j/16} in LDS); FP32 on the
+// e^{-x^2}: FP64 by the table-driven exponential (tab: 2^{j/64} in LDS); FP32 on the
 // hardware exp2, e^{-x^2} = 2^{-x^2 log2 e}.
-__device__ __forceinline__ double profile(double x, const double *tab) { return exp_tab16(-(x * x), tab); }
+__device__ __forceinline__ double profile(double x, const double *tab) { return exp_tab64(-(x * x), tab); }
 __device__ __forceinline__ float profile(float x, const double *)
 {
     return __builtin_amdgcn_exp2f(-(x * x) * 1.44269504088896340736f);
 }
 
-// e^{-x^2} at a node of a wave's sweep (uniform control flow).  Beyond x^2 = 746 the FP64
-// value above is exactly 0, so where every lane of the wave is that far in the wing the
-// exponential is skipped without changing any result.  (The FP32 exponential is cheaper
-// than the vote and branch, measured.)
-__device__ __forceinline__ double profile_far(double x, const double *tab)
+// Doppler offset a x_q - b.  (FP32 rounds the product, as it always has.)
+template <bool F32>
+__device__ __forceinline__ typename Bulk<F32>::T doppler(typename Bulk<F32>::T a, typename Bulk<F32>::T xq,
+                                                         typename Bulk<F32>::T b)
 {
-    return __all(x * x > 746.0) ? 0.0 : profile(x, tab);
+    if constexpr (F32)
+        return a * xq - b;
+    else
+        return fma(a, xq, -b);
 }
-__device__ __forceinline__ float profile_far(float x, const double *tab) { return profile(x, tab); }
 
 template <bool TRACK>
 __device__ __forceinline__ void rescale(HalfState &st)
@@ -96,49 +208,41 @@ __device__ __forceinline__ void rescale(HalfState &st)
 // becomes, for Q = N/D and y = Y/D,
 //   N' = N + h D,  Y' = Y + S h D,  D' = D + D_+ N'
 // (products and sums of non-negative numbers only).  The node coefficients a are
-// chi dz / (2 sqrt 2), so P = a_prev + a_t = D_+ / sqrt 2, and the state is carried as
+// chi dz / (2 sqrt 2), so Pp = a_prev + a_t = D_+ / sqrt 2, and the state is carried as
 // n = sqrt 2 N, y~ = sqrt 2 Y, d = D, which turns the update into
 //   n' = n + (P_- + P) d,  y~' = y~ + S (P_- + P) d,  d' = d + P n'
 // with no constant factors; Q = n/(sqrt 2 d), y = y~/(sqrt 2 d), and the factor sqrt 2
-// cancels in every quantity formed at the origin.  RENORM rescales n, d, y~ by the power
-// of two that brings d into [0.5, 1), which is exact.
-template <bool F32, bool RENORM, bool TRACK = false>
-__device__ __forceinline__ void elim_step(typename Bulk<F32>::T a_t, typename Bulk<F32>::T S_t,
-                                          typename Bulk<F32>::T &a_prev, typename Bulk<F32>::T &S_e,
-                                          HalfState &st)
+// cancels in every quantity formed at the origin.  S_row is the source of the row being
+// eliminated.  The weight t d is not formed (but for the band operator's record): with S t as a
+// factor of its own the new n, y~ and d are two dependent multiply-adds from the old d.
+template <bool TRACK = false>
+__device__ __forceinline__ void elim_p(double Pp, double S_row, HalfState &st)
 {
-    const double Pp = (double)(a_prev + a_t);
-    const double hd = (st.Hm + Pp) * st.D;
-    st.N = st.N + hd;
-    st.Y = fma((double)S_e, hd, st.Y);
+    const double t = st.Hm + Pp;
+    if (TRACK) {
+        st.hd = t * st.D;
+        st.Sl = S_row;
+    }
+    st.N = fma(t, st.D, st.N);
+    st.Y = fma(S_row * t, st.D, st.Y);
     st.D = fma(Pp, st.N, st.D);
     st.Hm = Pp;
-    if (TRACK) {
-        st.hd = hd;
-        st.Sl = (double)S_e;
-    }
-    a_prev = a_t;
-    S_e = S_t;
-    if (RENORM) rescale<TRACK>(st);
 }
 
 // Per-line state of a lane during a half sweep.
-// (The opacity at the current node is k_cur g_cur, recomputed where needed: the same
-// product the node's step used, so the same bits.)
-template <typename T, int LPL>
+template <int LPL>
 struct LineState {
     HalfState st[LPL];
-    T k_cur[LPL], S_e[LPL];
     int m_last;   // sub-intervals of the last segment (the one ending at O)
 };
 
-// A compiler barrier: LDS values read after it are loaded again instead of being kept in
+// A compiler barrier: values read after it are loaded again instead of being kept in
 // registers across the code before it (it emits no instruction).
 __device__ __forceinline__ void reload_fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
 
-// Rescale the lanes whose state passed 2^500 (in any of their lines).
-template <int LPL, bool TRACK, typename T>
-__device__ __forceinline__ void rescale_if_big(LineState<T, LPL> &ls)
+// Rescale the lanes whose state passed 2^300 (in any of their lines).
+template <int LPL, bool TRACK>
+__device__ __forceinline__ void rescale_if_big(LineState<LPL> &ls)
 {
     bool big = false;
 #pragma unroll
@@ -148,101 +252,6 @@ __device__ __forceinline__ void rescale_if_big(LineState<T, LPL> &ls)
         for (int l = 0; l < LPL; ++l) rescale<TRACK>(ls.st[l]);
     }
 }
-
-// One recurrence step of all LPL lines: g <- g r, r <- r c (shared), then the linear
-// kappa dz/4 and S of each line and its elimination step.
-template <bool F32, int LPL, bool RENORM, bool TRACK = false>
-__device__ __forceinline__ void recur_step(double &g, double &r, double c, double (&kq)[LPL],
-                                           const double (&dkq)[LPL], double (&St)[LPL],
-                                           const double (&dS)[LPL], typename Bulk<F32>::T (&a_prev)[LPL],
-                                           LineState<typename Bulk<F32>::T, LPL> &ls)
-{
-    g *= r;
-    r *= c;
-#pragma unroll
-    for (int l = 0; l < LPL; ++l) {
-        kq[l] += dkq[l];
-        St[l] += dS[l];
-        elim_step<F32, RENORM, TRACK>(kq[l] * g, St[l], a_prev[l], ls.S_e[l], ls.st[l]);
-    }
-}
-
-// The elimination step of elim_step with the segment's P = D_+ / sqrt 2 given and the
-// source S_row of the row being eliminated; nothing is carried to the next step but the
-// state (the lean form of the sweeps without the band operator's record).
-__device__ __forceinline__ void elim_p(double Pp, double S_row, HalfState &st)
-{
-    const double hd = (st.Hm + Pp) * st.D;
-    st.N = st.N + hd;
-    st.Y = fma(S_row, hd, st.Y);
-    st.D = fma(Pp, st.N, st.D);
-    st.Hm = Pp;
-}
-
-// short_node skips the profile's exponential where the whole wave is beyond its range
-// if SHORT_VOTE is set.  It is not: the vote is a wave-wide branch on a vector result at
-// every node, whose wait costs more than the exponentials it saves on a disc.  For the
-// same reason the segment loop checks for rescaling after every second node only (every
-// fourth measured slower: its extra test costs more than the check), and tests for the
-// end of a run on a scalar count taken at the run's start rather than on the next staged
-// record (disc10 FP64 sweep 5.50 -> 4.90 s for the three together).
-constexpr bool SHORT_VOTE = false;
-
-// One segment without sub-steps, to staged node r1 (the segment's dzq given): the
-// profile g1 of this lane at r1, r1's kappa and S of the lane's lines (k1, S1), and every
-// line's step with P = (kappa_0 g0 + kappa_1 g1) dzq and the row source S0 (in FP32 formed
-// as the general path forms it, so that both segment modes give the same bits).  A loop over
-// segments that calls this twice per iteration with the (g, k, S) sets swapped copies no
-// registers between segments.
-template <bool F32, int LPL, bool CHECK = true>
-__device__ __forceinline__ void short_node(const NodeRec<typename Bulk<F32>::T, 2 * LPL> &r1,
-                                           typename Bulk<F32>::T dzq, typename Bulk<F32>::T xq,
-                                           const double *tab, int grp, typename Bulk<F32>::T g0,
-                                           typename Bulk<F32>::T &g1, const typename Bulk<F32>::T (&k0)[LPL],
-                                           typename Bulk<F32>::T (&k1)[LPL], const typename Bulk<F32>::T (&S0)[LPL],
-                                           typename Bulk<F32>::T (&S1)[LPL], LineState<typename Bulk<F32>::T, LPL> &ls)
-{
-    using T = typename Bulk<F32>::T;
-    const T xn = r1.a * xq - r1.b;
-    if constexpr (SHORT_VOTE)
-        g1 = profile_far(xn, tab);
-    else
-        g1 = profile(xn, tab);
-#pragma unroll
-    for (int l = 0; l < LPL; ++l) {
-        const int c = grp * LPL + l;
-        k1[l] = r1.kap[c];
-        S1[l] = r1.S[c];
-        T Pp;
-        if constexpr (F32)
-            Pp = (k0[l] * g0) * dzq + (k1[l] * g1) * dzq;   // as the general path forms it, bit for bit
-        else
-            Pp = fma(k0[l], g0, k1[l] * g1) * dzq;
-        elim_p((double)Pp, (double)S0[l], ls.st[l]);
-    }
-    if (CHECK) rescale_if_big<LPL, false>(ls);
-}
-
-// The profile at a sub-step node: with the far-wing vote in the long-segment mode, without
-// it in the short mode (whose segments are rarely all in the far wing; the vote's branch
-// costs more there than the exponentials it saves).
-template <bool COLLAPSE, typename T>
-__device__ __forceinline__ T profile_sub(T x, const double *tab)
-{
-    if constexpr (COLLAPSE)
-        return profile_far(x, tab);
-    else
-        return profile(x, tab);
-}
-
-// Runs of segments without sub-steps take the loop of short_node (not in the long-segment
-// mode, whose far-wing collapse measured faster without it).
-template <bool F32, bool COLLAPSE>
-constexpr bool SHORT_LOOP = !COLLAPSE;
-// Sub-step segments: the form of the loop that alternates two sets of optical depths
-// (LEAN) or the one that carries a_prev and S_e through elim_step.
-template <bool F32, bool COLLAPSE>
-constexpr bool LEAN_SUBSTEPS = true;
 
 // Whether a segment lies beyond the line's range at every frequency of the quadrature, so
 // that the sweep may cross it in one step without opacity.  Along it the offset
@@ -274,23 +283,38 @@ __device__ __forceinline__ bool far_segment(bool in, double a0, double b0, doubl
 
 // Half-sweep along ray `ray` from its far end to O for Doppler offset xq of this lane.
 // The result is left in ls.st (one HalfState per line of the lane).  nexec counts the
-// elimination steps the wave executes (a collapsed far-wing segment counts as one).
-// COLLAPSE: the long-segment mode (profile recurrence).
-template <bool F32, int LPL, bool COLLAPSE, bool TRACK = false>
-__device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename Bulk<F32>::T, 2 * LPL> *rec,
-                                          const double *tab, int64_t O, int ray,
-                                          typename Bulk<F32>::T xq, int grp, int line0, int nlw,
-                                          LineState<typename Bulk<F32>::T, LPL> &ls, int64_t &nexec)
+// elimination steps the wave executes (a run of far-wing segments counts as one).
+// LONG: the long-segment mode, whose sub-steps take the profile by recurrence (FP64 only: the
+// FP32 exponential is one instruction).
+//
+// Carried from node to node: the node's values V (see Node), its offset x_cur and
+// profile g_cur, and per line c: in FP64 kappa, with P = kappa_0 (g_0 dzq) + kappa_1 (g_1 dzq),
+// which takes the two products with dzq once for all lines; in FP32 kappa g, whose
+// P = (kappa_0 g_0) dzq + (kappa_1 g_1) dzq rounds every product (sub-nodes: kappa (g dzq)).
+// Control flow is uniform, on masks and counts that the staging lanes left in scalar
+// registers; the only branch on a vector result is the check for rescaling.
+// Up to three lines leave registers for two profiles at a time, which hide each other's
+// latency: a sphere of 30,000 points 0.91 ms against 1.02 one by one, the FP64 outflow 4.4
+// against 5.0; with five lines it is the other way round (the disc 77 ms one by one, 89 with
+// pairs of sub-nodes, 100 with pairs of segments too).  FP32's long mode, where most segments
+// have sub-steps, is better without the pairs of segments (outflow 3.70 against 3.75 ms).
+template <bool F32, int LPL, bool LONG, bool TRACK = false>
+__device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32>::T *rec, const double *tab, int64_t O,
+                                          int ray, typename Bulk<F32>::T xq, int grp, int line0, int nlw,
+                                          LineState<LPL> &ls, int64_t &nexec)
 {
     using T = typename Bulk<F32>::T;
     using T2 = typename Bulk<F32>::T2;
-    constexpr int NLW = 2 * LPL;
+    constexpr bool kRows = kRowValues<F32, LPL, LONG>, kPairs = LPL == 1 || (LPL <= 3 && !(F32 && LONG));
+    using Nd = Node<LPL, kRows>;
+    using Vals = NodeVals<T, LPL, kRows>;
     const T2 *lc = reinterpret_cast<const T2 *>(a.lc);
     const int lane = threadIdx.x;
     const int ns = a.ns;   // nodes staged per round (2..64)
+    const NodeReader<T, LPL, kRows> node(rec, grp, lane);
 #pragma unroll
     for (int l = 0; l < LPL; ++l) {
-        // Q = 1, y = I_in at the far boundary (in the scaled state of elim_step)
+        // Q = 1, y = I_in at the far boundary (in the scaled state of elim_p)
         const int li = grp * LPL + l;
         ls.st[l].N = kSqrt2;
         ls.st[l].D = 1.0;
@@ -306,10 +330,8 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename 
     const int64_t beg = a.roff[base];
     const int L = (int)(a.roff[base + 1] - beg);
     if (L == 0) return;
-    // x_cur, g_cur: Doppler offset and profile at the current node; travel bounds how far
-    // x moved (any lane) since g was last evaluated exactly
-    T x_cur = 0, g_cur = 0;
-    double travel = 0.0;
+    T x_cur = 0, g_cur = 0, c[LPL];
+    float travel = 0.0f;   // bounds how far x moved (any lane) since g was last evaluated exactly
     for (int b0 = 0; b0 < L; b0 += ns - 1) {
         __syncthreads();
         // ---- stage nodes b0 .. b0+ns-1 in sweep order (far end first, O last)
@@ -319,349 +341,283 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename 
         const bool load = lane < ns && s <= L;
         if (load) {
             cidx = (s < L) ? (int64_t)a.rcells[beg + (L - 1 - s)] : O;
-            const CellRec c = a.cell[cidx];
+            const CellRec cc = a.cell[cidx];
             // O's record and the ray's direction are read again for each staging round (from
             // the caches) rather than held in registers through the sweep
             reload_fence();
             const CellRec cO = a.cell[O];
             const double nx = a.dir[3 * ray], ny = a.dir[3 * ray + 1], nz = a.dir[3 * ray + 2];
-            double dx = c.px - cO.px, dy = c.py - cO.py, dz = c.pz - cO.pz;
+            double dx = cc.px - cO.px, dy = cc.py - cO.py, dz = cc.pz - cO.pz;
             Zs = (dx * nx + dy * ny) + dz * nz;
-            double dvx = c.vx - cO.vx, dvy = c.vy - cO.vy, dvz = c.vz - cO.vz;
+            double dvx = cc.vx - cO.vx, dvy = cc.vy - cO.vy, dvz = cc.vz - cO.vz;
             sv = (dvx * nx + dvy * ny) + dvz * nz;
-            vw = c.vw;
+            vw = cc.vw;
             an = cO.vw / vw;
             bn = sv / vw;
         }
         const double Zn = __shfl_down(Zs, 1), sn = __shfl_down(sv, 1), vwn = __shfl_down(vw, 1);
         const double an1 = __shfl_down(an, 1), bn1 = __shfl_down(bn, 1);
+        const bool seg = s < L && lane < ns - 1;   // this lane's node starts a segment of the round
         // segments of this round that every frequency crosses beyond the line's range
-        const unsigned long long far_mask =
-            __ballot(far_segment<F32>(s < L && lane < ns - 1, an, bn, an1, bn1, Zs - Zn, a.xq_max,
-                                      load ? a.far[cidx] : float2{0.f, 0.f}));
-        int m_seg = 1;   // sub-intervals of this lane's segment (1 where it has none)
+        const unsigned long long far_mask = __ballot(
+            far_segment<F32>(seg, an, bn, an1, bn1, Zs - Zn, a.xq_max, load ? a.far[cidx] : float2{0.f, 0.f}));
+        int m_seg = 1, K_seg = 64;   // sub-intervals, and the restart interval of the recurrence (0: direct)
+        float dx_seg = 0.0f;         // bound on |dx| over every frequency
         if (load) {
-            NodeRec<T, NLW> r;
-            r.a = (T)an;
-            r.b = (T)bn;
+            T *w = rec + lane * Nd::kStride;
 #pragma unroll
-            for (int l = 0; l < NLW; ++l) {
-                T2 cl = l < nlw ? lc[cidx * a.n_lines + line0 + l] : T2{0, 0};
-                r.kap[l] = cl.x;
-                r.S[l] = cl.y;
+            for (int l = 0; l < 2 * LPL; ++l) {
+                const T2 cl = l < nlw ? lc[cidx * a.n_lines + line0 + l] : T2{0, 0};
+                w[(l / LPL) * 2 * LPL + l % LPL] = cl.x;
+                w[(l / LPL) * 2 * LPL + LPL + l % LPL] = cl.y;
             }
-            r.m = 1;
-            r.K = 64;
-            r.dzq = 0;
-            r.da = r.db = r.maxdx = 0;
-            r.inv_m = 1;
-            if (s < L && lane < ns - 1) {
+            double im = 1.0, dzq = 0.0;
+            if (seg) {
                 // velocity sub-steps (Sec. 3.2): split when the projected velocity changes
                 // by more than f_sub of the smaller line-width speed
                 const double ds = fabs(sn - sv);
                 const double thr = a.f_sub * fmin(vw, vwn);
-                int m = 1;
                 if (ds > thr) {
                     const double mr = ceil(ds / thr);
-                    m = mr < (double)kMaxSub ? (int)mr : kMaxSub;
+                    m_seg = mr < (double)kMaxSub ? (int)mr : kMaxSub;
                 }
-                const double im = 1.0 / (double)m;
-                m_seg = m;
-                r.m = m;
-                r.inv_m = (T)im;
-                r.dzq = (T)(kInv2Sqrt2 * (Zs - Zn) * im);
-                r.da = (T)((an1 - an) * im);
-                r.db = (T)((bn1 - bn) * im);
-                // bound on |dx| over every frequency of the quadrature; the recurrence of
-                // the profile restarts after at most 16 widths of travel in x
-                const double maxdx = (fabs(an1 - an) * a.xq_max + fabs(bn1 - bn)) * im;
-                r.maxdx = (T)maxdx;
-                r.K = maxdx > 4.0 ? 0 : (maxdx > 0.25 ? (int)(16.0 / maxdx) : 64);
+                im = 1.0 / (double)m_seg;
+                dzq = kInv2Sqrt2 * (Zs - Zn) * im;
+                if (LONG && !F32) {
+                    // the recurrence of the profile restarts after at most 16 widths of travel (and
+                    // divides by dzq at the segment's end)
+                    const double maxdx = (fabs(an1 - an) * a.xq_max + fabs(bn1 - bn)) * im;
+                    dx_seg = (float)maxdx * 1.0000002f;
+                    K_seg = maxdx > 4.0 || !(dzq > 1e-200) ? 0 : (maxdx > 0.25 ? (int)(16.0 / maxdx) : 64);
+                }
             }
-            rec[lane] = r;
+            w[Nd::kCommon] = (T)an;
+            w[Nd::kCommon + 1] = (T)bn;
+            w[Nd::kCommon + 2] = (T)dzq;
+            w[Nd::kCommon + 3] = (T)im;
+            w[Nd::kCommon + 4] = (T)((an1 - an) * im);
+            w[Nd::kCommon + 5] = (T)((bn1 - bn) * im);
         }
+        const unsigned long long sub_mask = __ballot(m_seg > 1);
         const int nseg = min(ns - 1, L - b0);
-        // short mode: the segments that end a run of segments without sub-steps (those with
-        // sub-steps, in the far wing, or past the round's last)
-        unsigned long long run_end = 0;
-        if constexpr (SHORT_LOOP<F32, COLLAPSE>)
-            run_end = __ballot(!(lane < nseg && m_seg == 1)) | far_mask;
         __syncthreads();
         // ---- sweep the staged segments
+        Vals V = node.values(0);
         if (b0 == 0) {
-            x_cur = rec[0].a * xq - rec[0].b;
+            x_cur = doppler<F32>(node.template own<0>(0, V), xq, node.template own<1>(0, V));
             g_cur = profile(x_cur, tab);
-#pragma unroll
-            for (int l = 0; l < LPL; ++l) {
-                ls.k_cur[l] = rec[0].kap[grp * LPL + l];
-                ls.S_e[l] = rec[0].S[grp * LPL + l];
-            }
         }
+        unrolled<LPL>([&](auto l) { c[l] = F32 ? V.template kap<l>() * g_cur : V.template kap<l>(); });
+        Vals V1;
+        if (kRows) V1 = node.values(1);   // the next node, read one ahead
         for (int i = 0; i < nseg; ++i) {
             if ((far_mask >> i) & 1) {
                 // a run of far-wing segments, eliminated in one step (see far_segment; the
                 // segment that ends at O, whose step the band operator records, is never one:
                 // O's own offsets lie within the quadrature)
                 i += (int)__builtin_ctzll(~(far_mask >> i));
-#pragma unroll
-                for (int l = 0; l < LPL; ++l) {
-                    elim_p(0.0, (double)ls.S_e[l], ls.st[l]);
-                    ls.k_cur[l] = rec[i].kap[grp * LPL + l];
-                    ls.S_e[l] = rec[i].S[grp * LPL + l];
-                }
+                unrolled<LPL>([&](auto l) { elim_p<false>(0.0, (double)V.template src<l>(), ls.st[l]); });
                 rescale_if_big<LPL, TRACK>(ls);
-                x_cur = rec[i].a * xq - rec[i].b;
+                V = node.values(i);
+                x_cur = doppler<F32>(node.template own<0>(i, V), xq, node.template own<1>(i, V));
                 g_cur = profile(x_cur, tab);
-                travel = 0.0;
+                unrolled<LPL>([&](auto l) { c[l] = F32 ? V.template kap<l>() * g_cur : V.template kap<l>(); });
+                travel = 0.0f;
                 ++nexec;
-                --i;
-                continue;
+                if (i >= nseg) break;
+                if (kRows) V1 = node.values(i + 1);
             }
-            if (!TRACK && SHORT_LOOP<F32, COLLAPSE> && !((run_end >> i) & 1)) {
-                // a run of segments without sub-steps (most of a disc's rays): one profile
-                // evaluation per node and one step per line (short_node), two segments per
-                // iteration so that the node values alternate between the A and B sets
-                T gA = g_cur, gB = 0;
-                T kA[LPL], kB[LPL], SA[LPL], SB[LPL];
-#pragma unroll
-                for (int l = 0; l < LPL; ++l) {
-                    kA[l] = ls.k_cur[l];
-                    SA[l] = ls.S_e[l];
-                }
-                // the run's length is known at its start (>= 1): the test between segments is on a
-                // scalar count, not on the next record
-                int run = (int)__builtin_ctzll(run_end >> i);
-                // two segments per iteration (the sets alternate A -> B -> A ...); the state is
-                // checked for rescaling after the second and where the run ends
-                for (;;) {
-                    short_node<F32, LPL, false>(rec[i + 1], rec[i].dzq, xq, tab, grp, gA, gB, kA, kB, SA, SB, ls);
-                    ++nexec;
-                    ++i;
-                    if (--run == 0) {
-                        rescale_if_big<LPL, false>(ls);
-                        gA = gB;
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l) {
-                            kA[l] = kB[l];
-                            SA[l] = SB[l];
+            if (!kRows) V1 = node.values(i + 1);
+            if (kPairs && !TRACK && i + 1 < nseg && (((far_mask | sub_mask) >> i) & 3) == 0) {
+                // a run of segments without sub-steps, two at a time: both profiles first, which do
+                // not depend on the eliminations (an odd last one takes the general path)
+                const unsigned long long ends = (far_mask | sub_mask) >> i;
+                const int left = nseg - i, run = kRows ? 2 : (ends ? min((int)__builtin_ctzll(ends), left) : left) & ~1;
+                nexec += run;
+                for (int k = run; k > 0; k -= 2, i += 2) {
+                    if (!kRows && k < run) V1 = node.values(i + 1);
+                    const Vals V2 = node.values(i + 2);
+                    const T dz0 = node.template own<2>(i, V), dz1 = node.template own<2>(i + 1, V1);
+                    const T x1 = doppler<F32>(node.template own<0>(i + 1, V1), xq, node.template own<1>(i + 1, V1));
+                    const T x2 = doppler<F32>(node.template own<0>(i + 2, V2), xq, node.template own<1>(i + 2, V2));
+                    const T g1 = profile(x1, tab), g2 = profile(x2, tab);
+                    const T G00 = g_cur * dz0, G01 = g1 * dz0, G10 = g1 * dz1, G11 = g2 * dz1;
+                    unrolled<LPL>([&](auto l) {
+                        const T k1 = V1.template kap<l>(), k2 = V2.template kap<l>();
+                        const double S0 = (double)V.template src<l>(), S1 = (double)V1.template src<l>();
+                        if constexpr (F32) {
+                            const T u1 = k1 * g1, u2 = k2 * g2;
+                            elim_p((double)(c[l] * dz0 + u1 * dz0), S0, ls.st[l]);
+                            elim_p((double)(u1 * dz1 + u2 * dz1), S1, ls.st[l]);
+                            c[l] = u2;
+                        } else {
+                            elim_p(fma(c[l], G00, k1 * G01), S0, ls.st[l]);
+                            elim_p(fma(k1, G10, k2 * G11), S1, ls.st[l]);
+                            c[l] = k2;
                         }
-                        break;
-                    }
-                    short_node<F32, LPL, false>(rec[i + 1], rec[i].dzq, xq, tab, grp, gB, gA, kB, kA, SB, SA, ls);
-                    ++nexec;
-                    ++i;
-                    rescale_if_big<LPL, false>(ls);
-                    if (--run == 0) break;
-                }
-                g_cur = gA;
-                x_cur = rec[i].a * xq - rec[i].b;   // the same bits as the last xn
-#pragma unroll
-                for (int l = 0; l < LPL; ++l) {
-                    ls.k_cur[l] = kA[l];
-                    ls.S_e[l] = SA[l];
-                }
-                travel = 0.0;
-                --i;
-                continue;
-            }
-            if (TRACK && SHORT_LOOP<F32, COLLAPSE> && !((run_end >> i) & 1)) {
-                // a run of segments without sub-steps (most of a disc's rays): one step per
-                // node with the profile evaluated there, in a loop of its own (FP64 short-
-                // segment mode; the FP32 form, whose exponential is one instruction, and the
-                // long-segment mode measured faster without it)
-                do {
-                    const T dzq = rec[i].dzq;
-                    const T xn = rec[i + 1].a * xq - rec[i + 1].b;
-                    const T gn = profile_far(xn, tab);
-#pragma unroll
-                    for (int l = 0; l < LPL; ++l) {
-                        const T kn = rec[i + 1].kap[grp * LPL + l];
-                        T a_prev = (ls.k_cur[l] * g_cur) * dzq;
-                        const T chi_n = kn * gn;
-                        elim_step<F32, false, TRACK>(chi_n * dzq, rec[i + 1].S[grp * LPL + l], a_prev, ls.S_e[l],
-                                                     ls.st[l]);
-                        ls.k_cur[l] = kn;
-                    }
+                    });
                     rescale_if_big<LPL, TRACK>(ls);
-                    x_cur = xn;
-                    g_cur = gn;
-                    ++nexec;
-                    ++i;
-                } while (!((run_end >> i) & 1));
-                travel = 0.0;
-                ls.m_last = 1;
+                    g_cur = g2;
+                    x_cur = x2;
+                    V = V2;
+                    if (kRows) V1 = node.values(min(i + 3, ns - 1));
+                }
+                travel = 0.0f;
                 --i;
                 continue;
             }
-            const int m = __builtin_amdgcn_readfirstlane(rec[i].m);   // (uniform: scalar loop control)
-            const T dzq = rec[i].dzq;
-            const T xn = rec[i + 1].a * xq - rec[i + 1].b;
-            // kn, Sn: the end node's data for the sub-step increments; read again (after a
-            // reload_fence) for the end node's own step, so they are not held meanwhile
-            T kn[LPL], Sn[LPL], a_prev[LPL];
+            const T dzq = node.template own<2>(i, V);
+            const T xn = doppler<F32>(node.template own<0>(i + 1, V1), xq, node.template own<1>(i + 1, V1));
+            // the segment's first node: G = g dzq (FP64), or every line's kappa g dzq (FP32)
+            T G = g_cur * dzq, gn = 0;
+            Vals Vr = V;   // the values of the row to be eliminated next
+            if (F32) unrolled<LPL>([&](auto l) { c[l] = c[l] * dzq; });
+            int m = 1;
+            bool have_gn = false;
+            if ((sub_mask >> i) & 1) {
+                m = __builtin_amdgcn_readlane(m_seg, i);
+                const T im = node.template own<3>(i, V);
+                const T dx = F32 ? node.template own<4>(i, V) * xq - node.template own<5>(i, V) : (xn - x_cur) * im;
+                Vals dV;
 #pragma unroll
-            for (int l = 0; l < LPL; ++l) {
-                kn[l] = rec[i + 1].kap[grp * LPL + l];
-                Sn[l] = rec[i + 1].S[grp * LPL + l];
-                a_prev[l] = (ls.k_cur[l] * g_cur) * dzq;
-            }
-            nexec += m;
-            T gn;
-            {
-                const T im = rec[i].inv_m;
-                const T dx = rec[i].da * xq - rec[i].db;
-                const int K = rec[i].K;
-                // direct evaluation where the recurrence would not pay for its two
-                // exponentials (no or one sub-step node) or cannot be used (K == 0)
-                if (!TRACK && LEAN_SUBSTEPS<F32, COLLAPSE> && (F32 || !COLLAPSE || K == 0 || m <= 2)) {
-                    // sub-node j: x = x_cur + j dx, kappa and S linear in j; two sub-nodes per
-                    // iteration, the step's P formed from the optical depths a at both ends
-                    // (alternating between a_prev and aB) and the row's S recomputed from j, so
-                    // that nothing else is carried from one sub-step to the next
-                    T S0[LPL], dk[LPL], dS[LPL], aB[LPL];
+                for (int k = 0; k < Vals::kN; ++k) dV.v[k] = (V1.v[k] - V.v[k]) * im;
+                // the values of sub-node j, and its step with G = g dzq there
+                auto at = [&](T t) {
+                    Vals w;
 #pragma unroll
-                    for (int l = 0; l < LPL; ++l) {
-                        S0[l] = ls.S_e[l];
-                        dk[l] = (kn[l] - ls.k_cur[l]) * im;
-                        dS[l] = (Sn[l] - S0[l]) * im;
-                    }
+                    for (int k = 0; k < Vals::kN; ++k) w.v[k] = fma(t, dV.v[k], V.v[k]);
+                    return w;
+                };
+                auto sub_node = [&](const Vals &w, T G1) {
+                    const NodeVals<double, LPL, kRows> Sr = in_fp64<LPL, kRows>(Vr);
+                    unrolled<LPL>([&](auto l) {
+                        const T k = w.template kap<l>();
+                        if constexpr (F32) {
+                            const T a1 = k * G1;
+                            elim_p<TRACK>((double)(c[l] + a1), Sr.template src<l>(), ls.st[l]);
+                            c[l] = a1;
+                        } else {
+                            elim_p<TRACK>(fma(c[l], G, k * G1), Sr.template src<l>(), ls.st[l]);
+                            c[l] = k;
+                        }
+                    });
+                    G = G1;
+                    Vr = w;
+                };
+                const int K = LONG && !F32 ? __builtin_amdgcn_readlane(K_seg, i) : 0;
+                if (F32 || !LONG || K == 0 || m <= 2) {
+                    // direct evaluation: the only form of the short mode, and where the recurrence
+                    // would not pay for its two exponentials or cannot be used
                     int j = 1;
-                    for (; j + 1 < m; j += 2) {
-                        const T t1 = (T)j, t2 = (T)(j + 1);
-                        const T g1 = profile_sub<COLLAPSE>(fma(t1, dx, x_cur), tab) * dzq;
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l) {
-                            aB[l] = fma(t1, dk[l], ls.k_cur[l]) * g1;
-                            elim_p((double)(a_prev[l] + aB[l]), (double)fma(t1 - (T)1, dS[l], S0[l]), ls.st[l]);
+                    if constexpr (LPL <= 3)
+                        for (; j + 1 < m; j += 2) {
+                            const T t1 = (T)j, t2 = (T)(j + 1);
+                            const T G1 = profile(fma(t1, dx, x_cur), tab) * dzq;
+                            const T G2 = profile(fma(t2, dx, x_cur), tab) * dzq;
+                            sub_node(at(t1), G1);
+                            sub_node(at(t2), G2);
+                            if (((j + 1) & 2) == 0) rescale_if_big<LPL, TRACK>(ls);   // (the end node checks too)
                         }
-                        const T g2 = profile_sub<COLLAPSE>(fma(t2, dx, x_cur), tab) * dzq;
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l) {
-                            a_prev[l] = fma(t2, dk[l], ls.k_cur[l]) * g2;
-                            elim_p((double)(aB[l] + a_prev[l]), (double)fma(t1, dS[l], S0[l]), ls.st[l]);
-                        }
-                        if (((j + 1) & 3) == 0) rescale_if_big<LPL, false>(ls);   // (the end node checks too)
+                    for (; j < m; ++j) {
+                        const T t = (T)j;
+                        sub_node(at(t), profile(fma(t, dx, x_cur), tab) * dzq);
+                        if ((j & 3) == 0) rescale_if_big<LPL, TRACK>(ls);
                     }
-                    if (j < m) {
-                        const T t1 = (T)j;
-                        const T g1 = profile_sub<COLLAPSE>(fma(t1, dx, x_cur), tab) * dzq;
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l) {
-                            aB[l] = fma(t1, dk[l], ls.k_cur[l]) * g1;
-                            elim_p((double)(a_prev[l] + aB[l]), (double)fma(t1 - (T)1, dS[l], S0[l]), ls.st[l]);
-                            a_prev[l] = aB[l];
-                        }
-                    }
-                    // the source of the last sub-node, whose row the end node's step eliminates
-#pragma unroll
-                    for (int l = 0; l < LPL; ++l) ls.S_e[l] = fma((T)(m - 1), dS[l], S0[l]);
-                    gn = profile_sub<COLLAPSE>(xn, tab);
-                    travel = 0.0;
-                } else if ((TRACK || !LEAN_SUBSTEPS<F32, COLLAPSE>) && (F32 || !COLLAPSE || K == 0 || m <= 2)) {
-                    T S0[LPL], dk[LPL], dS[LPL];
-#pragma unroll
-                    for (int l = 0; l < LPL; ++l) {
-                        S0[l] = ls.S_e[l];
-                        dk[l] = (kn[l] - ls.k_cur[l]) * im;
-                        dS[l] = (Sn[l] - S0[l]) * im;
-                    }
-                    for (int j = 1; j < m; ++j) {
-                        const T tj = (T)j;
-                        const T gq = profile_far(x_cur + tj * dx, tab) * dzq;
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l)
-                            elim_step<F32, false, TRACK>((ls.k_cur[l] + tj * dk[l]) * gq, S0[l] + tj * dS[l],
-                                                         a_prev[l], ls.S_e[l], ls.st[l]);
-                        if ((j & 3) == 0) rescale_if_big<LPL, TRACK>(ls);   // (the end node checks too)
-                    }
-                    gn = profile_far(xn, tab);
-                    travel = 0.0;
-                } else {
+                } else if constexpr (LONG && !F32) {
                     // x is linear in the sub-step index j, so g_j = e^{-x_j^2} obeys
-                    // g_{j+1} = g_j r_j, r_{j+1} = r_j c with r_j = e^{-2 x_j dx - dx^2} and
-                    // c = e^{-2 dx^2}.  Values are recomputed exactly whenever x may have
+                    // g_{j+1} = g_j r_j, r_{j+1} = r_j q with r_j = e^{-2 x_j dx - dx^2} and
+                    // q = e^{-2 dx^2}.  Values are recomputed exactly whenever x may have
                     // moved by more than 16 widths since the last exact value, so one that
                     // underflowed (|x| > 27) cannot hide a profile above e^{-121}.
-                    const double mdx = (double)rec[i].maxdx;
+                    const float mdx = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dx_seg), i));
                     const double u2 = 2.0 * dx * dx;
-                    const double c = mdx <= 0.5 ? exp_neg_small(u2) : exp_tab16(-u2, tab);
-                    // (kq starts at kappa dzq of the segment's first node, which k_cur keeps
-                    // until the segment ends, so restarts recompute it instead of holding it)
-                    // (restarts take S of the segment's first node from LDS again: S_e held it
-                    // when the segment began)
-                    double dkq[LPL], dS[LPL], kq[LPL], St[LPL];
-#pragma unroll
-                    for (int l = 0; l < LPL; ++l) {
-                        dkq[l] = (double)((kn[l] - ls.k_cur[l]) * im * dzq);
-                        dS[l] = (double)((Sn[l] - ls.S_e[l]) * im);
-                        kq[l] = (double)(ls.k_cur[l] * dzq);
-                        St[l] = (double)ls.S_e[l];
-                    }
-                    double g = g_cur, r = exp_tab16(fmin(-(2.0 * x_cur + dx) * dx, 700.0), tab);
+                    const double q = mdx <= 0.5f ? exp_neg_small(u2) : exp_tab64(-u2, tab);
+                    double r = exp_tab64(fmin(-(2.0 * x_cur + dx) * dx, 700.0), tab);
+                    double Gj = G;
+                    Vals w = V;
                     int budget = K;
-                    if (mdx > 0.0) budget = (int)fminf((16.0f - (float)travel) * __builtin_amdgcn_rcpf((float)mdx),
-                                                       (float)K);
+                    if (mdx > 0.0f) budget = (int)fminf((16.0f - travel) * __builtin_amdgcn_rcpf(mdx), (float)K);
                     if (budget < 1) {
-                        g = profile((double)x_cur, tab);
-                        travel = 0.0;
+                        Gj = profile(x_cur, tab) * dzq;
+                        travel = 0.0f;
                         budget = K;
                     }
                     int j = 0;
                     for (;;) {
                         const int jend = min(j + budget, m);
                         const int jint = min(jend, m - 1);
-                        int jj = j;
-                        for (; jj + 3 < jint; jj += 4) {
-                            recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
-                            recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
-                            recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
-                            recur_step<F32, LPL, true, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
+                        auto recur = [&] {
+                            Gj *= r;
+                            r *= q;
+#pragma unroll
+                            for (int v = 0; v < Vals::kN; ++v) w.v[v] += dV.v[v];
+                            sub_node(w, Gj);
+                        };
+                        int k = j;
+                        for (; k + 3 < jint; k += 4) {
+                            recur();
+                            recur();
+                            recur();
+                            recur();
+                            rescale_if_big<LPL, TRACK>(ls);
                         }
-                        // the last 0-3 steps in straight-line code (checked for rescaling
-                        // after the segment's end node)
-                        const int rem = jint - jj;
-                        if (rem >= 2) {
-                            recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
-                            recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
+                        // the last 0-3 steps in straight-line code
+                        if (jint - k >= 2) {
+                            recur();
+                            recur();
                         }
-                        if (rem & 1) recur_step<F32, LPL, false, TRACK>(g, r, c, kq, dkq, St, dS, a_prev, ls);
-                        travel += mdx * (double)(jint - j);
+                        if ((jint - k) & 1) recur();
+                        travel += mdx * (float)(jint - j);
                         j = jint;
                         if (jend == m) {
-                            g *= r;          // the cell at the end of the segment
+                            gn = Gj * r;     // the cell at the end of the segment (times dzq)
+                            have_gn = true;
                             travel += mdx;
                             break;
                         }
-                        rescale_if_big<LPL, TRACK>(ls);
-                        const double xj = fma((double)j, dx, (double)x_cur);
-                        g = exp_tab16(-(xj * xj), tab);
-                        r = exp_tab16(fmin(-(2.0 * xj + dx) * dx, 700.0), tab);
-                        reload_fence();
-#pragma unroll
-                        for (int l = 0; l < LPL; ++l) {
-                            kq[l] = fma((double)j, dkq[l], (double)(ls.k_cur[l] * dzq));
-                            St[l] = fma((double)j, dS[l], (double)rec[i].S[grp * LPL + l]);
-                        }
-                        travel = 0.0;
+                        const double xj = fma((double)j, dx, x_cur);
+                        Gj = exp_tab64(-(xj * xj), tab) * dzq;
+                        r = exp_tab64(fmin(-(2.0 * xj + dx) * dx, 700.0), tab);
+                        w = at((double)j);
+                        travel = 0.0f;
                         budget = K;
                     }
-                    gn = g;
                 }
             }
-            reload_fence();
-#pragma unroll
-            for (int l = 0; l < LPL; ++l) {
-                const T kn_e = rec[i + 1].kap[grp * LPL + l];
-                const T chi_n = kn_e * gn;
-                elim_step<F32, false, TRACK>(chi_n * dzq, rec[i + 1].S[grp * LPL + l], a_prev[l], ls.S_e[l],
-                                             ls.st[l]);
-                ls.k_cur[l] = kn_e;
+            nexec += m;
+            // the cell node at the end of the segment
+            T G1;
+            if (LONG && !F32 && have_gn) {
+                G1 = gn;
+                g_cur = gn * rcp_refined(dzq);
+            } else {
+                g_cur = profile(xn, tab);
+                G1 = g_cur * dzq;
+                travel = 0.0f;
             }
-            rescale_if_big<LPL, TRACK>(ls);
+            Vals Vn;
+            if (kRows) Vn = node.values(min(i + 2, ns - 1));
+            {
+                const NodeVals<double, LPL, kRows> Sr = in_fp64<LPL, kRows>(Vr);
+                unrolled<LPL>([&](auto l) {
+                    const T k = V1.template kap<l>();
+                    if constexpr (F32) {
+                        const T u = k * g_cur;
+                        elim_p<TRACK>((double)(c[l] + u * dzq), Sr.template src<l>(), ls.st[l]);
+                        c[l] = u;
+                    } else {
+                        elim_p<TRACK>(fma(c[l], G, k * G1), Sr.template src<l>(), ls.st[l]);
+                        c[l] = k;
+                    }
+                });
+            }
+            if (m > 1 || (i & 3) == 3) rescale_if_big<LPL, TRACK>(ls);
             x_cur = xn;
-            g_cur = gn;
+            V = V1;
+            if (kRows) V1 = Vn;
             if (TRACK) ls.m_last = m;
         }
+        rescale_if_big<LPL, TRACK>(ls);
     }
 }
 
@@ -672,15 +628,13 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, NodeRec<typename 
 // Lanes: with two groups, group g takes lanes 32 g .. 32 g + n_q - 1 (one frequency each)
 // and lines line0 + g LPL ...; with one group, lanes 0..63 take frequencies c 64 + lane of
 // chunk c.
-// red: LDS rows [3][LPL][64].  Each lane keeps the first half sweep's Q, y and last
-// optical-depth step in its column until the second half sweep ends (freeing registers in
-// the sweep); then the lanes write their contributions to J, L* and Jeff of each line
-// there, and lane q LPL + l of each group sums row (q, l) over the group's frequencies in
-// index order and adds it to its one accumulator (one register, not three per line).
-template <bool F32, int LPL, bool COLLAPSE, bool BAND = false>
+// After both half sweeps the lanes write their contributions to J, L* and Jeff of each line to
+// LDS rows [3][LPL][64] (in the staged nodes' place), and lane q LPL + l of each group sums row
+// (q, l) over the group's frequencies in index order and adds it to its one accumulator (one
+// register, not three per line).
+template <bool F32, int LPL, bool LONG, bool BAND = false>
 __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w, int p_beg, int p_end,
-                                           NodeRec<typename Bulk<F32>::T, 2 * LPL> *rec,
-                                           double (*red)[LPL][kWave], const double *tab)
+                                           double *smem, const double *tab)
 {
     using T = typename Bulk<F32>::T;
     using T2 = typename Bulk<F32>::T2;
@@ -704,7 +658,10 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
     // BAND lanes col0 + 3 LPL + q LPL + l (q < 2) accumulate Jb and Ld
     Acc acc = 0;
     const int rq = sub / LPL, rl = sub - rq * LPL;   // the row this lane sums
-    LineState<T, LPL> ls;
+    // LDS: the staged nodes during the sweeps, the rows of contributions after them
+    T *rec = reinterpret_cast<T *>(smem);
+    auto red = reinterpret_cast<double (*)[LPL][kWave]>(smem);
+    LineState<LPL> ls;
     unsigned long long my_exec = 0;   // executed node-frequency steps of this lane
     for (int p = p_beg; p < p_end; ++p) {
         const int r = a.pair_r[p], rb = a.anti[r];
@@ -715,21 +672,22 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
             const double wq = act ? a.qw[nidx] : 0.0;
             // u pairs I(n, x) with I(-n, -x): the antipode sweeps at the mirrored offset
             int64_t nex = 0;
+            double Q0[LPL], y0[LPL], H0[LPL];   // the first half's Q, y and last optical-depth step / sqrt 2
             double hdf[LPL], Sf[LPL];
             int mf = 1;
             // the two halves (unrolled: measured faster than one compiled sweep in a loop)
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                half_sweep<F32, LPL, COLLAPSE, BAND>(a, rec, tab, O, half ? rb : r, (T)(half ? -xq : xq), grp,
+                half_sweep<F32, LPL, LONG, BAND>(a, rec, tab, O, half ? rb : r, (T)(half ? -xq : xq), grp,
                                                      line0, nlw, ls, nex);
                 if (half) break;
                 if (BAND) mf = ls.m_last;
 #pragma unroll
                 for (int l = 0; l < LPL; ++l) {
-                    const double id = 1.0 / ls.st[l].D;
-                    red[0][l][lane] = ls.st[l].N * id;   // Q of the first half
-                    red[1][l][lane] = ls.st[l].Y * id;   // y
-                    red[2][l][lane] = ls.st[l].Hm;       // its last optical-depth step / sqrt 2
+                    const double id = rcp_refined(ls.st[l].D);
+                    Q0[l] = ls.st[l].N * id;
+                    y0[l] = ls.st[l].Y * id;
+                    H0[l] = ls.st[l].Hm;
                     if (BAND) {
                         hdf[l] = ls.st[l].hd * id;
                         Sf[l] = ls.st[l].Sl;
@@ -748,10 +706,10 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
             for (int l = 0; l < LPL; ++l) {
                 const int li = grp * LPL + l;
                 const double S_O = (double)lc[O * a.n_lines + line0 + (li < nlw ? li : 0)].y;
-                const double id = 1.0 / ls.st[l].D;
-                const double h = red[2][l][lane] + ls.st[l].Hm;
-                const double inv = 1.0 / (h + fma(ls.st[l].N, id, red[0][l][lane]));
-                const double yy = fma(ls.st[l].Y, id, red[1][l][lane]);
+                const double id = rcp_refined(ls.st[l].D);
+                const double h = H0[l] + ls.st[l].Hm;
+                const double inv = rcp_refined(h + fma(ls.st[l].N, id, Q0[l]));
+                const double yy = fma(ls.st[l].Y, id, y0[l]);
                 const bool on = act && lact[l];
                 vJ[l] = on ? wq * (fma(h, S_O, yy) * inv) : 0.0;
                 vL[l] = on ? wq * (h * inv) : 0.0;
@@ -768,7 +726,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
                     nbb[l] = on ? wq * tb * imb : 0.0;
                 }
             }
-            // sums over the group's frequencies (the rows' first-half values are consumed)
+            // sums over the group's frequencies
             __syncthreads();
 #pragma unroll
             for (int l = 0; l < LPL; ++l) {
@@ -841,17 +799,14 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
     }
 }
 
-// Dynamic LDS of a formal-solve workgroup: the rows [3][LPL][64] (FP64), then ns staged
-// nodes.
-template <bool F32, int LPL>
-constexpr size_t fs_rows_bytes()
-{
-    return sizeof(double) * 3 * LPL * kWave;
-}
+// Dynamic LDS of a formal-solve workgroup: ns staged nodes, or the rows [3][LPL][64] (FP64)
+// that take their place.
 template <bool F32, int LPL>
 constexpr size_t fs_lds_bytes(int ns)
 {
-    return fs_rows_bytes<F32, LPL>() + (size_t)ns * sizeof(NodeRec<typename Bulk<F32>::T, 2 * LPL>);
+    const size_t rows = sizeof(double) * 3 * LPL * kWave;
+    const size_t nodes = (size_t)ns * Node<LPL, true>::kStride * sizeof(typename Bulk<F32>::T);
+    return rows > nodes ? rows : nodes;
 }
 
 // Work items are (point, line block), or with a.split > 1 the split parts of its ray pairs; a
@@ -865,16 +820,15 @@ constexpr size_t fs_lds_bytes(int ns)
 // clear the counter: spheres of 12,000 and 60,000 points 413 and 2402 us against 363 and 2340,
 // the outflow of 20,011 points 4.94 ms against 4.75, FP32 3.61 against 3.47; only five FP64
 // lines per lane, whose workgroups also set up spill space, gained 1% from it.)
-// W: waves per SIMD the register budget is built for.
-template <bool F32, int LPL, int W, bool COLLAPSE>
-__global__ __launch_bounds__(64, W) void k_formal_solve(SolveArgs a)
+// W: waves per SIMD the register budget is built for (up to two FP32 lines need so few that the
+// three-wave form is held to four: 3.53 ms for the FP32 outflow against 3.76).
+template <bool F32, int LPL, int W, bool LONG>
+__global__ __launch_bounds__(64, F32 && LPL <= 2 && W == 3 ? 4 : W) void k_formal_solve(SolveArgs a)
 {
     extern __shared__ double fs_smem[];
-    __shared__ double tab[16];
-    auto *red = reinterpret_cast<double (*)[LPL][kWave]>(fs_smem);
-    auto *rec = reinterpret_cast<NodeRec<typename Bulk<F32>::T, 2 * LPL> *>(fs_smem + 3 * LPL * kWave);
+    __shared__ double tab[64];
     if (!F32) {
-        if (threadIdx.x < 16) tab[threadIdx.x] = kExp2Sixteenths[threadIdx.x];
+        tab[threadIdx.x] = kExp2SixtyFourths[threadIdx.x];
         __syncthreads();
     }
     // (one call site for both forms: the sweep is compiled once)
@@ -892,8 +846,8 @@ __global__ __launch_bounds__(64, W) void k_formal_solve(SolveArgs a)
             const int64_t block = item - part * n_points;
             const int64_t rank = block / a.groups;
             const int64_t O = a.persistent ? (int64_t)a.order[rank] : rank;
-            solve_item<F32, LPL, COLLAPSE>(a, O, (int)(block - rank * a.groups), part * a.n_pairs / a.split,
-                                           (part + 1) * a.n_pairs / a.split, rec, red, tab);
+            solve_item<F32, LPL, LONG>(a, O, (int)(block - rank * a.groups), part * a.n_pairs / a.split,
+                                           (part + 1) * a.n_pairs / a.split, fs_smem, tab);
         }
     }
 }
@@ -925,14 +879,14 @@ __global__ __launch_bounds__(256) void k_pair_sums(SolveArgs a)
     (q == 0 ? a.J : q == 1 ? a.L : a.Jeff)[O * a.n_lines + line] = a.norm * (double)acc;
 }
 
-template <bool F32, int LPL, int W, bool COLLAPSE>
+template <bool F32, int LPL, int W, bool LONG>
 hipError_t launch_fs_variant(const SolveArgs &a, hipStream_t s)
 {
     const size_t lds = fs_lds_bytes<F32, LPL>(a.ns);
     const int64_t n_tiles = (a.n_blocks + a.tile - 1) / a.tile;
     // one workgroup per tile (bounded: a launch counts its threads in 32 bits)
     const unsigned grid = (unsigned)(std::min<int64_t>((n_tiles + 7) / 8, 1 << 22) * 8);
-    hipLaunchKernelGGL((k_formal_solve<F32, LPL, W, COLLAPSE>), dim3(grid), dim3(kWave), lds, s, a);
+    hipLaunchKernelGGL((k_formal_solve<F32, LPL, W, LONG>), dim3(grid), dim3(kWave), lds, s, a);
     if (a.split > 1) {
         const int64_t n = a.P * a.groups * a.ngrp * 3 * LPL;
         hipLaunchKernelGGL((k_pair_sums<F32, LPL>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
@@ -943,13 +897,15 @@ hipError_t launch_fs_variant(const SolveArgs &a, hipStream_t s)
 template <bool F32, int LPL>
 hipError_t launch_fs_lpl(const SolveArgs &a, hipStream_t s)
 {
+    // (in FP32 the modes differ in the pairs of segments only, see half_sweep)
+    const bool collapse = a.collapse && !(F32 && LPL >= 4);
     if (a.waves == 3)
-        return a.collapse ? launch_fs_variant<F32, LPL, 3, true>(a, s)
+        return collapse ? launch_fs_variant<F32, LPL, 3, true>(a, s)
                           : launch_fs_variant<F32, LPL, 3, false>(a, s);
     if (a.waves == 1)
-        return a.collapse ? launch_fs_variant<F32, LPL, 1, true>(a, s)
+        return collapse ? launch_fs_variant<F32, LPL, 1, true>(a, s)
                           : launch_fs_variant<F32, LPL, 1, false>(a, s);
-    return a.collapse ? launch_fs_variant<F32, LPL, 2, true>(a, s)
+    return collapse ? launch_fs_variant<F32, LPL, 2, true>(a, s)
                       : launch_fs_variant<F32, LPL, 2, false>(a, s);
 }
 

@@ -28,16 +28,14 @@ template <int LPL, bool LONG>
 __global__ __launch_bounds__(64, 2) void k_formal_solve_band(SolveArgs a)
 {
     extern __shared__ double fs_smem[];
-    __shared__ double tab[16];
-    auto *red = reinterpret_cast<double (*)[LPL][kWave]>(fs_smem);
-    auto *rec = reinterpret_cast<NodeRec<double, 2 * LPL> *>(fs_smem + 3 * LPL * kWave);
-    if (threadIdx.x < 16) tab[threadIdx.x] = kExp2Sixteenths[threadIdx.x];
+    __shared__ double tab[64];
+    tab[threadIdx.x] = kExp2SixtyFourths[threadIdx.x];
     __syncthreads();
     const int64_t nb8 = (a.n_blocks + 7) / 8;
     const int64_t lb = (int64_t)(blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);
     if (lb >= a.n_blocks) return;
     const int64_t O = lb / a.groups;
-    solve_item<false, LPL, LONG, true>(a, O, (int)(lb - O * a.groups), 0, a.n_pairs, rec, red, tab);
+    solve_item<false, LPL, LONG, true>(a, O, (int)(lb - O * a.groups), 0, a.n_pairs, fs_smem, tab);
 }
 
 hipError_t launch_formal_solve_band(const SolveArgs &a, hipStream_t s)
