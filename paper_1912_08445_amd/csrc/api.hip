@@ -213,11 +213,13 @@ size_t part_need(const SolveArgs &a, bool fp32)
 // (1.0) 1058 / 748, 10,000 (3.3) 667 / 632; discs of 1,000 (0.5) 5.70 / 3.21 ms, 5,000 (2.4)
 // 3.98 / 3.81, 10,000 with six pairs (4.9) 1.87 / 1.90; more items than that cost as much as
 // they bring (16 fillings: outflows 658 and 762 us of 632 and 748).
+int64_t split_items(const nlte_ctx *c, const SolveArgs &a) { return (int64_t)c->n_cu * 4 * a.waves * 8; }
+
 void set_split(nlte_ctx *c, SolveArgs &a, bool fp32)
 {
     a.split = 1;
     a.part = nullptr;
-    const int64_t items = a.P * a.groups, want = (int64_t)c->n_cu * 4 * a.waves * 8;
+    const int64_t items = a.P * a.groups, want = split_items(c, a);
     if (c->d_part && a.persistent && items < want && part_need(a, fp32) <= c->part_bytes) {
         a.split = (int)std::min<int64_t>((want + items - 1) / items, a.n_pairs);
         a.part = c->d_part;
@@ -584,17 +586,18 @@ nlte_status ensure_band(nlte_ctx *c)
         if ((st = dalloc(c, &c->d_Ln, (size_t)P * nl * R))) return st;
         if ((st = dalloc(c, &c->d_bLU, (size_t)P * n * n))) return st;
         if ((st = dalloc(c, &c->d_bcpl, (size_t)P * nl * R))) return st;
-        if ((st = dalloc(c, &c->d_bx0, (size_t)P * n))) return st;
-        if ((st = dalloc(c, &c->d_bpiv, (size_t)P * n))) return st;
-        if ((st = dalloc(c, &c->d_bvec, (size_t)P * n * 8))) return st;
-        if ((st = dalloc(c, &c->d_bpart, (size_t)band_dot_blocks(P) * 3))) return st;
-        if ((st = dalloc(c, &c->d_bdot, 3))) return st;
-        if ((st = dalloc(c, &c->d_bbad, 1))) return st;
-        if ((st = dalloc(c, &c->d_bmodel_bad, (size_t)c->n_models))) return st;
-        c->h_bmodel_bad.assign((size_t)c->n_models, 0);
-        if (!c->h_bdot) HIPCHK(c, hipHostMalloc((void **)&c->h_bdot, sizeof(double) * 3, hipHostMallocDefault));
-        if (!c->h_bbad)
-            HIPCHK(c, hipHostMalloc((void **)&c->h_bbad, sizeof(unsigned long long), hipHostMallocDefault));
+        // per-pair sums of a split band formal solve (at most the lines plus three idle slots)
+        const size_t pair_sums = (size_t)P * (nl + 3) * c->n_pairs * ((c->n_q + kWave - 1) / kWave) * 5;
+        c->bsum_count = pair_sums * sizeof(double) <= kPartBytes ? pair_sums : 0;
+        if (c->bsum_count > 0 && (st = dalloc(c, &c->d_bsum, c->bsum_count))) return st;
+        if ((st = dalloc(c, &c->d_bperm, (size_t)P))) return st;
+        if ((st = dalloc(c, &c->d_bvec, (size_t)P * n * 9))) return st;
+        if ((st = dalloc(c, &c->d_bpart, (size_t)band_blocks(P) * 7))) return st;
+        const size_t state = sizeof(BandState) + (size_t)c->n_models;
+        if ((st = dalloc(c, &c->d_bstate, state))) return st;
+        if (c->h_bstate) (void)hipHostFree(c->h_bstate);
+        c->h_bstate = nullptr;
+        HIPCHK(c, hipHostMalloc((void **)&c->h_bstate, state, hipHostMallocDefault));
         memcpy(c->band_dims, dims, sizeof dims);
         c->first_valid = false;
     }
@@ -617,8 +620,6 @@ nlte_status formal_solve_band_impl(nlte_ctx *c, const double *d_pops, double *d_
         a.lines_per_wave = a.ngrp * 2;
         a.groups = (c->n_lines + a.lines_per_wave - 1) / a.lines_per_wave;
     }
-    a.split = 1;
-    a.n_blocks = c->P * a.groups;
     {   // its own launch: FP64, a budget of two waves per SIMD, the same segment mode
         const SolveConfig keep = c->cfg;
         c->cfg.waves = 2;
@@ -627,29 +628,21 @@ nlte_status formal_solve_band_impl(nlte_ctx *c, const double *d_pops, double *d_
         a.persistent = 0;
         a.tile = 1;
     }
+    // few points: their pairs over several waves, as in the local solve (3,001 points of six
+    // pairs: 140 us without, 117 with)
+    const int64_t items = c->P * a.groups;
+    a.split = 1;
+    if (items < split_items(c, a) &&
+        (size_t)items * a.n_pairs * a.fchunks * 5 * a.lines_per_wave <= c->bsum_count) {
+        a.split = (int)std::min<int64_t>((split_items(c, a) + items - 1) / items, a.n_pairs);
+        a.part = c->d_bsum;
+    }
+    a.n_blocks = items * a.split;
     if (ali) a.model_done = c->d_model_done;
     a.Jb = c->d_Jb;
     a.Ld = c->d_Ld;
     a.Ln = c->d_Ln;
     HIPCHK(c, timed(c, c->st_formal, s, [&] { return launch_formal_solve_band(a, s); }));
-    return NLTE_OK;
-}
-
-// Weighted inner products (a_k, b_k), k < nd, into c->h_bdot (synchronises s).
-nlte_status band_dots(nlte_ctx *c, int nd, const double *a0, const double *b0, const double *a1, const double *b1,
-                      const double *a2, const double *b2, hipStream_t s)
-{
-    DotArgs d{};
-    d.a[0] = a0;
-    d.b[0] = b0;
-    d.a[1] = a1 ? a1 : a0;
-    d.b[1] = b1 ? b1 : b0;
-    d.a[2] = a2 ? a2 : a0;
-    d.b[2] = b2 ? b2 : b0;
-    d.nd = nd;
-    HIPCHK(c, launch_band_dots(d, c->d_cell, c->n_lev, c->P, c->d_bpart, c->d_bdot, s));
-    HIPCHK(c, hipMemcpyAsync(c->h_bdot, c->d_bdot, sizeof(double) * 3, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
     return NLTE_OK;
 }
 
@@ -666,7 +659,6 @@ nlte_status stateq_band_impl(nlte_ctx *c, const double *d_old, const double *d_J
 {
     const int n = c->n_lev;
     const int64_t N = c->P * n;
-    const double tol = 1e-13;
     *used = 0;
     *iters = 0;
     BandArgs b{};
@@ -677,77 +669,40 @@ nlte_status stateq_band_impl(nlte_ctx *c, const double *d_old, const double *d_J
     b.done = ali ? c->d_model_done : nullptr;
     b.model_of = c->d_model_of;
     b.LU = c->d_bLU;
-    b.piv = c->d_bpiv;
+    b.perm = c->d_bperm;
     b.cpl = c->d_bcpl;
-    b.x0 = c->d_bx0;
-    b.bad = c->d_bbad;
-    b.model_bad = c->d_bmodel_bad;
+    b.state = reinterpret_cast<BandState *>(c->d_bstate);
+    b.model_bad = c->d_bstate + sizeof(BandState);
     b.P = c->P;
     b.R = c->n_rays;
-    double *x = c->d_bvec, *r = x + N, *r0 = r + N, *p = r0 + N, *v = p + N, *sv = v + N, *t = sv + N, *w = t + N;
-    HIPCHK(c, launch_fill_u64(c->d_bbad, 1, 0ull, s));
-    HIPCHK(c, launch_fill_u8(c->d_bmodel_bad, c->n_models, 0, s));
-    HIPCHK(c, launch_band_setup(b, c->sp, c->d_cell, c->d_nh2, c->d_T, d_old, s));
-    HIPCHK(c, launch_band_mask(b, c->n_lines, s));
-    nlte_status st;
-    // x = K^-1 b; r = K^-1 b - (I + K^-1 C) x = -(K^-1 C) x
-    HIPCHK(c, launch_band_lin(x, 1.0, c->d_bx0, 0.0, c->d_bx0, 0.0, nullptr, N, s));
-    HIPCHK(c, launch_band_apply(b, c->sp, x, w, s));
-    HIPCHK(c, launch_band_lin(r, 1.0, x, -1.0, w, 0.0, nullptr, N, s));
-    HIPCHK(c, launch_band_lin(r0, 1.0, r, 0.0, r, 0.0, nullptr, N, s));
-    HIPCHK(c, launch_band_lin(p, 0.0, r, 0.0, r, 0.0, nullptr, N, s));
-    HIPCHK(c, launch_band_lin(v, 0.0, r, 0.0, r, 0.0, nullptr, N, s));
-    if ((st = band_dots(c, 3, r0, r, r, r, x, x, s))) return st;
-    double rho = 1.0, alpha = 1.0, omega = 1.0, rho1 = c->h_bdot[0];
-    bool ok = true;
-    bool conv = !(c->h_bdot[2] > 0.0) || c->h_bdot[1] <= tol * tol * c->h_bdot[2];
-    for (int it = 0; it < 200 && !conv && ok; ++it) {
-        *iters = it + 1;
-        if (!(rho1 != 0.0) || !std::isfinite(rho1)) {
-            ok = false;
-            break;
-        }
-        const double beta = (rho1 / rho) * (alpha / omega);
-        HIPCHK(c, launch_band_lin(p, 1.0, r, beta, p, -beta * omega, v, N, s));
-        HIPCHK(c, launch_band_apply(b, c->sp, p, v, s));
-        if ((st = band_dots(c, 1, r0, v, nullptr, nullptr, nullptr, nullptr, s))) return st;
-        const double sigma = c->h_bdot[0];
-        if (!(sigma != 0.0) || !std::isfinite(sigma)) {
-            ok = false;
-            break;
-        }
-        alpha = rho1 / sigma;
-        HIPCHK(c, launch_band_lin(sv, 1.0, r, -alpha, v, 0.0, nullptr, N, s));
-        if ((st = band_dots(c, 2, sv, sv, x, x, nullptr, nullptr, s))) return st;
-        if (c->h_bdot[0] <= tol * tol * c->h_bdot[1]) {
-            HIPCHK(c, launch_band_lin(x, 1.0, x, alpha, p, 0.0, nullptr, N, s));
-            conv = true;
-            break;
-        }
-        HIPCHK(c, launch_band_apply(b, c->sp, sv, t, s));
-        if ((st = band_dots(c, 2, t, sv, t, t, nullptr, nullptr, s))) return st;
-        if (!(c->h_bdot[1] > 0.0)) {
-            ok = false;
-            break;
-        }
-        omega = c->h_bdot[0] / c->h_bdot[1];
-        HIPCHK(c, launch_band_lin(x, 1.0, x, alpha, p, omega, sv, N, s));
-        HIPCHK(c, launch_band_lin(r, 1.0, sv, -omega, t, 0.0, nullptr, N, s));
-        if ((st = band_dots(c, 3, r0, r, r, r, x, x, s))) return st;
-        rho = rho1;
-        rho1 = c->h_bdot[0];
-        conv = c->h_bdot[1] <= tol * tol * c->h_bdot[2];
-        if (!(omega != 0.0)) ok = false;
+    b.nb = band_blocks(c->P);
+    double *vec = c->d_bvec;
+    for (double **q : {&b.x, &b.r, &b.r0, &b.p[0], &b.p[1], &b.v[0], &b.v[1], &b.s, &b.t}) {
+        *q = vec;
+        vec += N;
     }
-    ok = ok && conv;
-    int n_bad = c->n_models;
-    if (ok) {
-        HIPCHK(c, launch_band_check_models(x, n, c->P, c->d_model_of, c->d_bmodel_bad, s));
-        HIPCHK(c, hipMemcpyAsync(c->h_bmodel_bad.data(), c->d_bmodel_bad, (size_t)c->n_models, hipMemcpyDeviceToHost,
-                                 s));
+    b.part_p = c->d_bpart;
+    b.part_s = b.part_p + b.nb;
+    b.part_x = b.part_s + 3 * b.nb;
+    const size_t state_bytes = sizeof(BandState) + (size_t)c->n_models;
+    HIPCHK(c, launch_fill_u8(c->d_bstate, (int64_t)state_bytes, 0, s));
+    HIPCHK(c, launch_band_setup(b, c->sp, c->d_cell, c->d_nh2, c->d_T, d_old, s));
+    // four steps at a time until the device says how it ended (a step past the end costs three
+    // empty kernels, one too few a synchronisation)
+    const BandState &ended = *reinterpret_cast<const BandState *>(c->h_bstate);
+    const uint8_t *model_bad = c->h_bstate + sizeof(BandState);
+    for (int from = 0;; from += 4) {
+        HIPCHK(c, launch_band_steps(b, c->sp, c->d_cell, from, from + 4, s));
+        HIPCHK(c, launch_band_check_models(b.x, n, c->P, c->d_model_of, b.model_bad, b.state, s));
+        HIPCHK(c, hipMemcpyAsync(c->h_bstate, c->d_bstate, state_bytes, hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
+        if (ended.ended != 0) break;
+    }
+    *iters = ended.iters;
+    int n_bad = c->n_models;
+    if (ended.status == kBandConverged) {
         n_bad = 0;
-        for (uint8_t f : c->h_bmodel_bad) n_bad += f != 0;
+        for (int m = 0; m < c->n_models; ++m) n_bad += model_bad[m] != 0;
     }
     auto local = [&](double *out, ConvPartial *parts, unsigned long long *change) {
         return launch_stateq(c->sp, c->d_cell, c->d_nh2, c->d_T, c->P, c->params.use_alo, d_old, d_J, d_Jeff, d_L,
@@ -759,9 +714,9 @@ nlte_status stateq_band_impl(nlte_ctx *c, const double *d_old, const double *d_J
         HIPCHK(c, local(d_new, c->d_partials, ali ? c->d_model_change : nullptr));
         return NLTE_OK;
     }
-    if (n_bad > 0) HIPCHK(c, local(r0, nullptr, nullptr));   // r0 is free once the solve is done
+    if (n_bad > 0) HIPCHK(c, local(b.r0, nullptr, nullptr));   // r0 is free once the solve is done
     *used = c->n_models - n_bad;
-    HIPCHK(c, launch_band_finish(x, n_bad > 0 ? r0 : nullptr, n_bad > 0 ? c->d_bmodel_bad : nullptr, d_old, c->d_cell, n,
+    HIPCHK(c, launch_band_finish(b.x, n_bad > 0 ? b.r0 : nullptr, n_bad > 0 ? b.model_bad : nullptr, d_old, c->d_cell, n,
                                  c->P, d_new, d_flags, c->d_partials, ali ? c->d_model_done : nullptr, c->d_model_of,
                                  ali ? c->d_model_change : nullptr, s));
     return NLTE_OK;
@@ -980,15 +935,12 @@ void nlte_destroy(nlte_ctx *c)
     dfree(c->d_Ln);
     dfree(c->d_bLU);
     dfree(c->d_bcpl);
-    dfree(c->d_bx0);
-    dfree(c->d_bpiv);
+    dfree(c->d_bsum);
+    dfree(c->d_bperm);
     dfree(c->d_bvec);
     dfree(c->d_bpart);
-    dfree(c->d_bdot);
-    dfree(c->d_bbad);
-    dfree(c->d_bmodel_bad);
-    if (c->h_bdot) (void)hipHostFree(c->h_bdot);
-    if (c->h_bbad) (void)hipHostFree(c->h_bbad);
+    dfree(c->d_bstate);
+    if (c->h_bstate) (void)hipHostFree(c->h_bstate);
     dfree(c->d_ng_hist);
     dfree(c->d_ng_part);
     dfree(c->d_ng_coef);

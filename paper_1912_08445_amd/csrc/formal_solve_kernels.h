@@ -428,7 +428,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                 if (kRows) V1 = node.values(i + 1);
             }
             if (!kRows) V1 = node.values(i + 1);
-            if (kPairs && !TRACK && i + 1 < nseg && (((far_mask | sub_mask) >> i) & 3) == 0) {
+            if (kPairs && i + 1 < nseg && (((far_mask | sub_mask) >> i) & 3) == 0) {
                 // a run of segments without sub-steps, two at a time: both profiles first, which do
                 // not depend on the eliminations (an odd last one takes the general path)
                 const unsigned long long ends = (far_mask | sub_mask) >> i;
@@ -447,12 +447,12 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                         const double S0 = (double)V.template src<l>(), S1 = (double)V1.template src<l>();
                         if constexpr (F32) {
                             const T u1 = k1 * g1, u2 = k2 * g2;
-                            elim_p((double)(c[l] * dz0 + u1 * dz0), S0, ls.st[l]);
-                            elim_p((double)(u1 * dz1 + u2 * dz1), S1, ls.st[l]);
+                            elim_p<TRACK>((double)(c[l] * dz0 + u1 * dz0), S0, ls.st[l]);
+                            elim_p<TRACK>((double)(u1 * dz1 + u2 * dz1), S1, ls.st[l]);
                             c[l] = u2;
                         } else {
-                            elim_p(fma(c[l], G00, k1 * G01), S0, ls.st[l]);
-                            elim_p(fma(k1, G10, k2 * G11), S1, ls.st[l]);
+                            elim_p<TRACK>(fma(c[l], G00, k1 * G01), S0, ls.st[l]);
+                            elim_p<TRACK>(fma(k1, G10, k2 * G11), S1, ls.st[l]);
                             c[l] = k2;
                         }
                     });
@@ -463,6 +463,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                     if (kRows) V1 = node.values(min(i + 3, ns - 1));
                 }
                 travel = 0.0f;
+                if (TRACK) ls.m_last = 1;
                 --i;
                 continue;
             }
@@ -656,6 +657,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
     const int col0 = grp * width;                             // first lane of the group
     // lane col0 + q LPL + l (q < 3) accumulates quantity q (J, L*, Jeff) of line l; with
     // BAND lanes col0 + 3 LPL + q LPL + l (q < 2) accumulate Jb and Ld
+    constexpr int kSums = BAND ? 5 : 3;
     Acc acc = 0;
     const int rq = sub / LPL, rl = sub - rq * LPL;   // the row this lane sums
     // LDS: the staged nodes during the sweeps, the rows of contributions after them
@@ -735,16 +737,22 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
                 red[2][l][lane] = vE[l];
             }
             __syncthreads();
+            // (where another wave has the point's other pairs, k_pair_sums adds them in order)
+            Acc *part = nullptr;
+            if (a.split > 1) {
+                const int64_t row = ((O * a.groups + w) * a.n_pairs + p) * a.fchunks + c;
+                part = static_cast<Acc *>(a.part) + (row * ngrp + grp) * (kSums * LPL) + sub;
+            }
+            auto add = [&](Acc sum) {
+                if (part != nullptr)
+                    *part = sum;
+                else
+                    acc += sum;
+            };
             if (sub < 3 * LPL) {
                 Acc sum = 0;
                 for (int i = 0; i < nfq; ++i) sum += (Acc)red[rq][rl][col0 + i];
-                if (!BAND && a.split > 1) {
-                    // another wave has the point's other pairs: k_pair_sums adds them in order
-                    const int64_t row = ((O * a.groups + w) * a.n_pairs + p) * a.fchunks + c;
-                    static_cast<Acc *>(a.part)[(row * ngrp + grp) * (3 * LPL) + sub] = sum;
-                } else {
-                    acc += sum;
-                }
+                add(sum);
             }
             if (BAND) {
                 __syncthreads();
@@ -758,7 +766,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
                     const int q = (sub - 3 * LPL) / LPL, l = sub - 3 * LPL - q * LPL;
                     double sum = 0.0;
                     for (int i = 0; i < nfq; ++i) sum += red[q][l][col0 + i];
-                    acc += (Acc)sum;
+                    add((Acc)sum);
                 }
                 // couplings to the first cells along r and rb, per line summed over this
                 // group's frequencies (fixed order)
@@ -788,8 +796,8 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int64_t O, int w,
         for (int o = kWave / 2; o > 0; o >>= 1) my_exec += __shfl_xor(my_exec, o);
         if (lane == 0) atomicAdd(a.exec_steps, my_exec);
     }
-    if (!BAND && a.split > 1) return;
-    if (sub < (BAND ? 5 : 3) * LPL && rl < LPL) {
+    if (a.split > 1) return;
+    if (sub < kSums * LPL && rl < LPL) {
         const int q = sub / LPL, l = sub - q * LPL, li = grp * LPL + l;
         if (li < nlw) {
             const int64_t o = O * a.n_lines + line0 + li;
@@ -852,23 +860,23 @@ __global__ __launch_bounds__(64, F32 && LPL <= 2 && W == 3 ? 4 : W) void k_forma
     }
 }
 
-// J, L* and Jeff from the per-pair sums of a split launch, added in the order in which one
+// J, L* and Jeff (Q = 5: also Jb and Ld) from the per-pair sums of a split launch, added in the order in which one
 // wave would have met the pairs (the same bits).  One thread per (point, line block, lane
 // group, sum).
-template <bool F32, int LPL>
+template <bool F32, int LPL, int Q>
 __global__ __launch_bounds__(256) void k_pair_sums(SolveArgs a)
 {
     using Acc = typename Bulk<F32>::T;
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int slots = a.ngrp * 3 * LPL;
+    const int slots = a.ngrp * Q * LPL;
     if (t >= a.P * a.groups * slots) return;
     const int64_t block = t / slots;
     const int slot = (int)(t - block * slots);
     const int64_t O = block / a.groups;
     const int w = (int)(block - O * a.groups);
     if (a.model_done != nullptr && a.model_done[a.model_of[O]]) return;
-    const int grp = slot / (3 * LPL), q = (slot - grp * 3 * LPL) / LPL;
-    const int li = grp * LPL + (slot - grp * 3 * LPL - q * LPL);
+    const int grp = slot / (Q * LPL), q = (slot - grp * Q * LPL) / LPL;
+    const int li = grp * LPL + (slot - grp * Q * LPL - q * LPL);
     const int line = w * a.lines_per_wave + li;
     if (li >= a.lines_per_wave || line >= a.n_lines) return;
     const int rows = a.n_pairs * a.fchunks;
@@ -876,7 +884,16 @@ __global__ __launch_bounds__(256) void k_pair_sums(SolveArgs a)
     Acc acc = 0;
 #pragma unroll 8
     for (int i = 0; i < rows; ++i) acc += part[(int64_t)i * slots];
-    (q == 0 ? a.J : q == 1 ? a.L : a.Jeff)[O * a.n_lines + line] = a.norm * (double)acc;
+    double *out = q == 0 ? a.J : q == 1 ? a.L : q == 2 ? a.Jeff : q == 3 ? a.Jb : a.Ld;
+    out[O * a.n_lines + line] = a.norm * (double)acc;
+}
+
+template <bool F32, int LPL, int Q>
+hipError_t launch_pair_sums(const SolveArgs &a, hipStream_t s)
+{
+    const int64_t n = a.P * a.groups * a.ngrp * Q * LPL;
+    hipLaunchKernelGGL((k_pair_sums<F32, LPL, Q>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 template <bool F32, int LPL, int W, bool LONG>
@@ -888,8 +905,9 @@ hipError_t launch_fs_variant(const SolveArgs &a, hipStream_t s)
     const unsigned grid = (unsigned)(std::min<int64_t>((n_tiles + 7) / 8, 1 << 22) * 8);
     hipLaunchKernelGGL((k_formal_solve<F32, LPL, W, LONG>), dim3(grid), dim3(kWave), lds, s, a);
     if (a.split > 1) {
-        const int64_t n = a.P * a.groups * a.ngrp * 3 * LPL;
-        hipLaunchKernelGGL((k_pair_sums<F32, LPL>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_pair_sums<F32, LPL, 3>(a, s);
     }
     return hipGetLastError();
 }

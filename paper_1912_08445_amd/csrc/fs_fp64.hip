@@ -31,6 +31,15 @@ __global__ __launch_bounds__(64, 2) void k_formal_solve_band(SolveArgs a)
     __shared__ double tab[64];
     tab[threadIdx.x] = kExp2SixtyFourths[threadIdx.x];
     __syncthreads();
+    if (a.split > 1) {   // the parts of a point's pairs, points in decreasing cost (see k_formal_solve)
+        if (blockIdx.x >= a.n_blocks) return;
+        const int64_t n_points = a.n_blocks / a.split;
+        const int part = (int)(blockIdx.x / n_points);
+        const int64_t block = blockIdx.x - part * n_points, rank = block / a.groups;
+        solve_item<false, LPL, LONG, true>(a, a.order[rank], (int)(block - rank * a.groups), part * a.n_pairs / a.split,
+                                           (part + 1) * a.n_pairs / a.split, fs_smem, tab);
+        return;
+    }
     const int64_t nb8 = (a.n_blocks + 7) / 8;
     const int64_t lb = (int64_t)(blockIdx.x & 7) * nb8 + (blockIdx.x >> 3);
     if (lb >= a.n_blocks) return;
@@ -54,7 +63,9 @@ hipError_t launch_formal_solve_band(const SolveArgs &a, hipStream_t s)
         hipLaunchKernelGGL((k_formal_solve_band<2, false>), grid, dim3(kWave), (fs_lds_bytes<false, 2>(a.ns)), s, a);
     else
         return hipErrorInvalidValue;
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.split <= 1) return e;
+    return lpl == 1 ? launch_pair_sums<false, 1, 5>(a, s) : launch_pair_sums<false, 2, 5>(a, s);
 }
 
 }  // namespace nlte

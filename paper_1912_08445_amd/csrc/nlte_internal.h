@@ -100,25 +100,30 @@ struct SolveArgs {
 };
 
 // Coupled statistical equilibrium of the band ALO (see band.hip).
+// The coupled solve's scalars and how it ended (see band.hip); slots by the step's parity.
+enum { kBandConverged = 1, kBandFailed = 2 };
+struct BandState {
+    double rho[2], alpha[2], omega[2], xx;
+    int32_t ended;    // the kernel (counted from 1) that ended the solve; 0: still running
+    int32_t status;
+    int32_t iters;
+    int32_t pad;
+};
+
 struct BandArgs {
     const double *Jb, *Ld, *Ln;   // band formal-solve outputs
     const int32_t *first;         // [P][n_rays] first cell of each walk (-1: none)
     const uint8_t *done;          // converged models (held fixed; null: none)
     const int32_t *model_of;
     double *LU;                   // [P][n_lev][n_lev] factors of the points' own rate matrices
-    int32_t *piv;                 // [P][n_lev]
+    unsigned long long *perm;     // [P] their row swaps, 4 bits per column
     double *cpl;                  // [P][n_lines][n_rays] coupling coefficients
-    double *x0;                   // [P][n_lev] uncoupled solution
-    unsigned long long *bad;      // singular local matrices
+    double *x, *r, *r0, *p[2], *v[2], *s, *t;   // [P][n_lev] vectors of the solver
+    double *part_p, *part_s, *part_x;           // per-block sums [nb][1], [nb][3], [nb][3]
+    BandState *state;
     uint8_t *model_bad;           // [n_models] 1: the model takes the local solve this iteration
     int64_t P;
-    int R;
-};
-
-struct DotArgs {
-    const double *a[3];
-    const double *b[3];
-    int nd;
+    int R, nb;
 };
 
 // Formal solve with scattering (see scatter.hip).
@@ -305,14 +310,14 @@ struct nlte_ctx {
     int32_t *d_first = nullptr;          // [P][n_rays]
     bool first_valid = false;
     double *d_Jb = nullptr, *d_Ld = nullptr, *d_Ln = nullptr;
-    double *d_bLU = nullptr, *d_bcpl = nullptr, *d_bx0 = nullptr;
-    int32_t *d_bpiv = nullptr;
-    double *d_bvec = nullptr;            // 8 vectors of [P][n_lev]
-    double *d_bpart = nullptr, *d_bdot = nullptr, *h_bdot = nullptr;
-    unsigned long long *d_bbad = nullptr, *h_bbad = nullptr;
+    double *d_bLU = nullptr, *d_bcpl = nullptr;
+    unsigned long long *d_bperm = nullptr;
+    double *d_bsum = nullptr;            // per-pair sums of a split band formal solve [bsum_count]
+    size_t bsum_count = 0;
+    double *d_bvec = nullptr;            // 9 vectors of [P][n_lev]
+    double *d_bpart = nullptr;           // per-block sums [blocks][7]
     int64_t band_dims[5] = {0, 0, 0, 0, 0};   // P, n_lev, n_lines, n_rays, n_models the buffers were sized for
-    uint8_t *d_bmodel_bad = nullptr;     // [n_models]
-    std::vector<uint8_t> h_bmodel_bad;
+    uint8_t *d_bstate = nullptr, *h_bstate = nullptr;   // BandState, then model_bad [n_models]; pinned copy
 
     std::vector<double> dir_host;        // [n_rays][3] as set
 
@@ -435,15 +440,10 @@ hipError_t launch_conv_final(const ConvPartial *partials, int64_t n, ConvResult 
 hipError_t launch_first_cells(const int64_t *roff, const int32_t *rcells, int64_t n, int32_t *first, hipStream_t s);
 hipError_t launch_band_setup(const BandArgs &b, const SpeciesDev &sp, const CellRec *cell, const double *nh2,
                              const double *T, const double *old, hipStream_t s);
-hipError_t launch_band_apply(const BandArgs &b, const SpeciesDev &sp, const double *y, double *w, hipStream_t s);
-int64_t band_dot_blocks(int64_t P);
-hipError_t launch_band_dots(const DotArgs &d, const CellRec *cell, int n, int64_t P, double *part, double *out,
-                            hipStream_t s);
-hipError_t launch_band_lin(double *out, double a, const double *X, double b, const double *Y, double c,
-                           const double *Z, int64_t N, hipStream_t s);
+int band_blocks(int64_t P);   // per-block sums a solver kernel leaves
+hipError_t launch_band_steps(const BandArgs &b, const SpeciesDev &sp, const CellRec *cell, int from, int to, hipStream_t s);
 hipError_t launch_band_check_models(const double *x, int n, int64_t P, const int32_t *model_of, uint8_t *model_bad,
-                                   hipStream_t s);
-hipError_t launch_band_mask(const BandArgs &b, int n_lines, hipStream_t s);
+                                   const BandState *state, hipStream_t s);
 hipError_t launch_band_finish(const double *x, const double *local, const uint8_t *model_bad, const double *old,
                               const CellRec *cell, int n, int64_t P, double *pops_new, uint8_t *flags,
                               ConvPartial *partials, const uint8_t *done, const int32_t *model_of,
