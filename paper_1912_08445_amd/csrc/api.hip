@@ -757,6 +757,7 @@ nlte_status formal_solve_scat_impl(nlte_ctx *c, const double *d_pops, const doub
 {
     HIPCHK(c, launch_line_coef(c->sp, c->d_cell, d_pops, c->P, 0, c->d_lc, ali ? c->d_maser : nullptr, nullptr, nullptr, s));
     ScatArgs a{};
+    a.order = c->d_order;
     a.cell = c->d_cell;
     a.lc = c->d_lc;
     a.roff = c->d_roff;

@@ -148,6 +148,7 @@ struct ScatArgs {
     int q_uniform;           // 1: evenly spaced quadrature offsets
     const uint8_t *model_done;   // ALI only (null: solve every point)
     const int32_t *model_of;
+    const int32_t *order;        // [P] points in decreasing cost
 };
 
 // Image of the model along one ray direction (see image.hip).
