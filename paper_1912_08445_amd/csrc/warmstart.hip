@@ -413,7 +413,7 @@ hipError_t launch_mlp_forward(const void *frags, const float *theta, const MlpDi
 //                 gradient (FP32) go to global memory, feature-major with the batch rows
 //                 contiguous (Ht [kHRows][ld], DZt [kDRows][ld], ld = batch rounded up to 32);
 //   k_mlp_wgrad   the weight gradients dW_L = DZ_L^T H_L as products over the batch rows:
-//                 one wave per (16 x 16 tile, chunk of rows), partial sums per chunk;
+//                 one wave per (pair of 16 x 16 tiles, chunk of rows), partial sums per chunk;
 //   k_mlp_update  the chunks summed in order, Adam, and the new weights written into the
 //                 bfloat16 operands of the forward and backward products.
 // Rounding is where the single-kernel form had it: activations and output gradients are
@@ -423,9 +423,10 @@ constexpr int kHRows = 16 + 3 * kHid;                              // feature ro
 constexpr int kHOff[4] = {0, 16, 16 + kHid, 16 + 2 * kHid};        // input of layer L (8 inputs padded to 16)
 constexpr int kDRows = 3 * kHid + 16;                              // feature rows of DZt
 constexpr int kDOff[4] = {0, kHid, 2 * kHid, 3 * kHid};            // output gradient of layer L (n_out padded to 16)
-// weight-gradient tiles (16 outputs x 16 inputs): L1 8 x 1, L2 8 x 8, L3 8 x 8, L4 1 x 8
-constexpr int kTileBase[5] = {0, 8, 72, 136, 144};
-constexpr int kTiles = 144;
+// weight-gradient tiles (16 outputs x 16 inputs), two side by side where a layer has them:
+// L1 8 x 1, L2 8 x 8, L3 8 x 8, L4 1 x 8
+constexpr int kPairBase[4] = {0, 8, 40, 72};
+constexpr int kPairs = 76;
 constexpr int kChunkRows = 256;   // batch rows per weight-gradient chunk (more chunks up to kMaxChunks)
 constexpr int kMaxChunks = 128;
 
@@ -488,7 +489,10 @@ __global__ __launch_bounds__(256) void k_mlp_fwdbwd(const Frag *__restrict__ fra
 
     // tiles of 16 rows, the workgroup's weights kept in registers from one to the next
     const int64_t n_tiles = ld / 16;
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    for (int64_t slot = blockIdx.x; slot < n_tiles; slot += gridDim.x) {
+        // within whole rounds of 8 chunks, a chunk's 16 tiles to the XCD that takes its products
+        const int64_t round = slot & ~(int64_t)127, in = slot & 127;
+        const int64_t tile = round + 128 <= n_tiles ? round + (in & 7) * 16 + (in >> 3) : slot;
         const int64_t b = tile * 16 + i;   // batch row: the tiles' column i
         const bool valid = b < batch;
         const int64_t row = valid ? (start + b) % n : 0;
@@ -609,31 +613,41 @@ __global__ __launch_bounds__(256) void k_mlp_fwdbwd(const Frag *__restrict__ fra
     }
 }
 
-// Weight gradients of one 16 x 16 tile over one chunk of batch rows (blockIdx.x: tile,
-// blockIdx.y: chunk).  The A operand is the output gradients (rounded to bfloat16), the
-// B operand the layer's inputs; a lane loads its eight rows as two runs of four.  Tiles
-// of the first input column also sum the FP32 output gradients for the bias.  gpart
-// [chunks][n_params].
+// Weight gradients of two 16 x 16 tiles side by side (one where the layer has one column of
+// tiles) over one chunk of batch rows (blockIdx.x: pair of tiles, blockIdx.y: chunk).  The A
+// operand is the output gradients (rounded to bfloat16), which both tiles share, the B operand
+// the layer's inputs; a lane loads its eight rows as two runs of four.  Tiles of the first input
+// column also sum the FP32 output gradients for the bias.  gpart [chunks][n_params].
+// Reads of the operands bound it: with the chunks spread over all XCDs each of the 8 L2s
+// fetched all of Ht and DZt, 80 MB per step at a batch of 4,096.  A step there took 32 us (13, 11.5
+// and 6.4 in the three kernels); 29 with pairs of tiles and k_mlp_update's loads requested
+// together, 27 with a chunk's products on one XCD, 24 with its rows' forward and backward
+// pass on the same XCD.  Fewer than eight chunks would leave XCDs idle that way: spread.
 __global__ __launch_bounds__(64) void k_mlp_wgrad(MlpDims d, const unsigned short *__restrict__ Ht,
                                                    const float *__restrict__ DZt, int ld, int chunk,
-                                                   float *__restrict__ gpart)
+                                                   int S, float *__restrict__ gpart)
 {
-    const int tile = blockIdx.x, c = blockIdx.y;
-    const int L = tile < kTileBase[1] ? 0 : tile < kTileBase[2] ? 1 : tile < kTileBase[3] ? 2 : 3;
-    const int NT = L == 0 ? 1 : 8;
-    const int local = tile - kTileBase[L];
-    const int mt = local / NT, nt = local - mt * NT;
+    // workgroups go round-robin to the 8 XCDs: chunk c to XCD c mod 8 (S of them)
+    const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+    const int c = S < 8 ? (int)blockIdx.x / kPairs : x + 8 * (k / kPairs);
+    const int pair = S < 8 ? (int)blockIdx.x % kPairs : k % kPairs;
+    if (c >= S) return;
+    const int L = pair < kPairBase[1] ? 0 : pair < kPairBase[2] ? 1 : pair < kPairBase[3] ? 2 : 3;
+    const int local = pair - kPairBase[L];
+    const bool two = L > 0;
+    const int mt = two ? local / 4 : local, nt = two ? 2 * (local - 4 * mt) : 0;
     const int lane = threadIdx.x;
     const int i = lane & 15, g = lane >> 4;
     const float *arow = DZt + (int64_t)(kDOff[L] + 16 * mt + i) * ld;
     const unsigned short *brow = Ht + (int64_t)(kHOff[L] + 16 * nt + i) * ld;
+    const unsigned short *brow2 = two ? brow + (int64_t)16 * ld : brow;
     const int r_beg = c * chunk, r_end = min(ld, r_beg + chunk);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
     float bsum = 0.0f;
     // rows r0 + 16 q + 4 g + (0..3), q = 0, 1: the lane's eight K slots of one step
     struct Raw {
         float4 a0, a1;
-        uint2 b0, b1;
+        uint2 b0, b1, c0, c1;
     };
     auto fetch = [&](int r0) {
         Raw w;
@@ -641,10 +655,12 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(MlpDims d, const unsigned shor
         w.a1 = *reinterpret_cast<const float4 *>(arow + r0 + 16 + 4 * g);
         w.b0 = *reinterpret_cast<const uint2 *>(brow + r0 + 4 * g);
         w.b1 = *reinterpret_cast<const uint2 *>(brow + r0 + 16 + 4 * g);
+        w.c0 = *reinterpret_cast<const uint2 *>(brow2 + r0 + 4 * g);
+        w.c1 = *reinterpret_cast<const uint2 *>(brow2 + r0 + 16 + 4 * g);
         return w;
     };
     auto use = [&](const Raw &w) {
-        Frag fa, fb;
+        Frag fa;
         fa.v[0] = bf16_bits(w.a0.x);
         fa.v[1] = bf16_bits(w.a0.y);
         fa.v[2] = bf16_bits(w.a0.z);
@@ -653,16 +669,9 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(MlpDims d, const unsigned shor
         fa.v[5] = bf16_bits(w.a1.y);
         fa.v[6] = bf16_bits(w.a1.z);
         fa.v[7] = bf16_bits(w.a1.w);
-        fb.v[0] = (unsigned short)(w.b0.x & 0xFFFFu);
-        fb.v[1] = (unsigned short)(w.b0.x >> 16);
-        fb.v[2] = (unsigned short)(w.b0.y & 0xFFFFu);
-        fb.v[3] = (unsigned short)(w.b0.y >> 16);
-        fb.v[4] = (unsigned short)(w.b1.x & 0xFFFFu);
-        fb.v[5] = (unsigned short)(w.b1.x >> 16);
-        fb.v[6] = (unsigned short)(w.b1.y & 0xFFFFu);
-        fb.v[7] = (unsigned short)(w.b1.y >> 16);
         bsum += ((w.a0.x + w.a0.y) + (w.a0.z + w.a0.w)) + ((w.a1.x + w.a1.y) + (w.a1.z + w.a1.w));
-        acc = mfma(fa, fb, acc);
+        acc = mfma(fa, __builtin_bit_cast(Frag, uint4{w.b0.x, w.b0.y, w.b1.x, w.b1.y}), acc);
+        acc2 = mfma(fa, __builtin_bit_cast(Frag, uint4{w.c0.x, w.c0.y, w.c1.x, w.c1.y}), acc2);
     };
     int r0 = r_beg;
     // four steps' operands requested before the first of their products
@@ -680,6 +689,7 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(MlpDims d, const unsigned shor
     for (int j = 0; j < 4; ++j) {
         const int o = 16 * mt + 4 * g + j;
         if (o < d.out[L] && col < d.in[L]) gp[d.w_off[L] + (int64_t)o * d.in[L] + col] = acc[j];
+        if (two && o < d.out[L] && col + 16 < d.in[L]) gp[d.w_off[L] + (int64_t)o * d.in[L] + col + 16] = acc2[j];
     }
     if (nt == 0) {
         // output 16 mt + i: the row sums of the four lane groups, in order
@@ -709,8 +719,9 @@ hipError_t launch_mlp_train(const void *frags, const float *theta, const MlpDims
     if (e != hipSuccess) return e;
     const int S = mlp_chunks(ld);
     const int chunk = (ld / 32 + S - 1) / S * 32;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(kTiles, S), dim3(64), 0, s, d, (const unsigned short *)Ht,
-                       (const float *)DZt, ld, chunk, gpart);
+    const int slots = S < 8 ? S : (S + 7) / 8 * 8;
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(kPairs * slots), dim3(64), 0, s, d, (const unsigned short *)Ht,
+                       (const float *)DZt, ld, chunk, S, gpart);
     return hipGetLastError();
 }
 
@@ -719,7 +730,7 @@ hipError_t launch_mlp_train(const void *frags, const float *theta, const MlpDims
 // value written into its slot of the forward operands and, for layers 2-4, of the
 // backward (transposed) operands; the slots are those k_mlp_pack fills, found by
 // inverting its index map.  The first thread writes the batch loss (mean squared error).
-__global__ void k_mlp_update(float *__restrict__ theta, float *__restrict__ m, float *__restrict__ v,
+__global__ __launch_bounds__(kWave) void k_mlp_update(float *__restrict__ theta, float *__restrict__ m, float *__restrict__ v,
                              unsigned short *__restrict__ fslot, MlpDims d, const float *__restrict__ gpart, int S,
                              int update, float lr, float b1, float b2, float eps, float c1, float c2,
                              const float *__restrict__ lpart, int n_waves, float inv_count, float *__restrict__ loss,
@@ -728,28 +739,37 @@ __global__ void k_mlp_update(float *__restrict__ theta, float *__restrict__ m, f
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t np = d.n_params;
     if (blockIdx.x == 0 && loss) {
-        // the loss partials: thread t sums entries t, t + 256, ... in order, then a fixed tree
+        // the loss partials: sum t of 256 takes entries t, t + 256, ... in order, then a fixed tree
         __shared__ float red[256];
-        float sacc = 0.0f;
-        for (int w = threadIdx.x; w < n_waves; w += blockDim.x) sacc += lpart[w];
-        red[threadIdx.x] = sacc;
+        for (int t = threadIdx.x; t < 256; t += kWave) {
+            float sacc = 0.0f;
+            for (int w = t; w < n_waves; w += 256) sacc += lpart[w];
+            red[t] = sacc;
+        }
         __syncthreads();
-        for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        for (int h = 128; h > 0; h >>= 1) {
+            for (int t = threadIdx.x; t < h; t += kWave) red[t] += red[t + h];
             __syncthreads();
         }
         if (threadIdx.x == 0) *loss = red[0] * inv_count;
     }
     if (p >= np) return;
+    float m0 = 0.0f, v0 = 0.0f, t0 = 0.0f;
+    if (update) {
+        m0 = m[p];
+        v0 = v[p];
+        t0 = theta[p];
+    }
     float gsum = 0.0f;
+#pragma unroll 16
     for (int c = 0; c < S; ++c) gsum += gpart[(int64_t)c * np + p];
     if (grad_out) grad_out[p] = gsum;
     if (!update) return;
-    const float mm = b1 * m[p] + (1.0f - b1) * gsum;
-    const float vv = b2 * v[p] + (1.0f - b2) * gsum * gsum;
+    const float mm = b1 * m0 + (1.0f - b1) * gsum;
+    const float vv = b2 * v0 + (1.0f - b2) * gsum * gsum;
     m[p] = mm;
     v[p] = vv;
-    const float t = theta[p] - lr * (mm * c1) / (sqrtf(vv * c2) + eps);
+    const float t = t0 - lr * (mm * c1) / (sqrtf(vv * c2) + eps);
     theta[p] = t;
     int L = -1;
 #pragma unroll
@@ -757,8 +777,8 @@ __global__ void k_mlp_update(float *__restrict__ theta, float *__restrict__ m, f
         if (p >= d.w_off[l] && p < d.b_off[l]) L = l;
     if (L < 0) return;   // a bias: not in the packed operands
     const unsigned short tb = bf16_bits(t);
-    const int o = (int)((p - d.w_off[L]) / d.in[L]);
-    const int k = (int)((p - d.w_off[L]) - (int64_t)o * d.in[L]);
+    const unsigned e = (unsigned)(p - d.w_off[L]);
+    const int o = (int)(e / (unsigned)d.in[L]), k = (int)(e - (unsigned)o * (unsigned)d.in[L]);
     {
         // forward operand: row o of tile mt, reduction index k = kslot(s, g, j)
         const int KT = L == 0 ? 1 : 4;
@@ -783,7 +803,7 @@ hipError_t launch_mlp_update(float *theta, float *m, float *v, void *frags, cons
 {
     const int ld = mlp_ld(batch);
     const int64_t np = d.n_params;
-    hipLaunchKernelGGL(k_mlp_update, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, theta, m, v,
+    hipLaunchKernelGGL(k_mlp_update, dim3((unsigned)((np + kWave - 1) / kWave)), dim3(kWave), 0, s, theta, m, v,
                        (unsigned short *)frags, d, gpart, mlp_chunks(ld), update, lr, b1, b2, eps, c1, c2, lpart,
                        ld / 16, inv_count, loss, grad_out);
     return hipGetLastError();
