@@ -88,13 +88,13 @@ typedef struct {
                          FP64 formal solve whatever the precision; no graph replay.  Needs
                          use_alo.  0 */
     int long_segments; /* velocity sub-step segments (Sec. 3.2) in the formal solve: 1 = long
-                         segments: along a segment's sub-steps the line profile follows a
-                         multiplicative recurrence, and a segment that lies beyond the
-                         profile's range for every frequency of a wave is eliminated in one
-                         step (it has no opacity); 0 = short segments: every sub-step node
-                         evaluates its profile; -1 = by the trace (long when the cached walks
-                         average more than two elimination steps per cell).  The two agree
-                         to rounding.  -1 */
+                         segments: along a segment's sub-steps the FP64 line profile follows a
+                         multiplicative recurrence; 0 = short segments: every sub-step node
+                         evaluates its profile; -1 = by the lines per lane and the trace (long
+                         for up to three lines per lane when the cached walks average more
+                         than 3.5 elimination steps per cell, 2 in the FP32 form).  Either way
+                         a run of segments beyond the line's range for every frequency is
+                         eliminated in one step.  The two agree to rounding.  -1 */
     int stage_nodes;  /* ray nodes a formal-solve wave stages in LDS at a time, 2..64 (0 = by
                          rule: the most that keep the register budget's occupancy).  0 */
     int tile_points;  /* formal-solve work items (point, line block) a workgroup takes at a time,
@@ -264,14 +264,14 @@ nlte_status nlte_formal_solve_dev(nlte_ctx *ctx, const double *d_pops, double *d
  * For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): nlte_formal_solve_dev with the same
  * arguments, results and kernels, which allocates nothing.  Its scratch (the per-(point,
- * line) opacity and source staging and the work-queue counter) lives in a fixed array of
- * 64 MiB in the library's device code, one per GPU, held until the process ends, instead
- * of the context's buffers.  It takes P * n_lines <= 4,194,288 in FP64 (8,388,576 in the
- * FP32 form); larger models get NLTE_E_INVALID_ARG (use nlte_formal_solve_dev).  Every
- * call on one GPU shares that GPU's array, from any context: calls that overlap on one GPU
- * (two streams, two threads) race and must be ordered by the caller.  The counter is
- * cleared by a kernel on `stream` at each call (no memset node), so the call can be
- * captured.  No kernel timing or step counting (params.profile is ignored).
+ * line) opacity and source staging, and two exponents per point for the far-wing test)
+ * lives in fixed arrays of 64 MiB each in the library's device code, one of each per GPU,
+ * held until the process ends, instead of the context's buffers.  It takes P * n_lines
+ * <= 4,194,288 in FP64 (8,388,576 in the FP32 form); larger models get NLTE_E_INVALID_ARG
+ * (use nlte_formal_solve_dev).  Every call on one GPU shares that GPU's arrays, from any
+ * context: calls that overlap on one GPU (two streams, two threads) race and must be
+ * ordered by the caller.  The call can be captured (kernels only, no memset node) and
+ * never splits the pairs of few points.  No kernel timing or step counting (params.profile is ignored).
  */
 nlte_status nlte_formal_solve_noalloc_dev(nlte_ctx *ctx, const double *d_pops, double *d_J,
                                           double *d_Jeff, double *d_Lstar, void *stream);
@@ -402,8 +402,8 @@ nlte_status nlte_get_model_status(nlte_ctx *ctx, int32_t *iterations, uint8_t *c
 
 /* The formal-solve launch the current parameters resolve to (after the rules for the
  * choices left at 0 or -1): lines per lane, waves per SIMD of the register budget, long
- * segments (0/1), ray nodes staged per round, persistent (0/1), work items per workgroup
- * grab; any pointer may be NULL.  Needs nlte_trace (the collapse rule reads the trace). */
+ * segments (0/1), ray nodes staged per round, persistent (0/1), work items per workgroup;
+ * any pointer may be NULL.  Needs nlte_trace (the segment rule reads the trace). */
 nlte_status nlte_get_launch(nlte_ctx *ctx, int *lines_per_lane, int *waves_per_simd, int *long_segments,
                             int *stage_nodes, int *persistent, int *tile_points);
 

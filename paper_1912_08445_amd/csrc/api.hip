@@ -1014,7 +1014,7 @@ nlte_status nlte_set_species(nlte_ctx *c, int n_lev, const double *E, const doub
 
     // packed device layout: ints first, then doubles
     const int ni = 2 * n_lines + 2 * n_coll;
-    const int nd = 5 * n_lines + 2 * n_lev + n_T + n_coll * n_T;
+    const int nd = 5 * n_lines + 2 * n_lev + n_T + n_coll * n_T + 2 * n_coll;
     std::vector<int32_t> hi(ni);
     std::vector<double> hd(nd);
     c->nu.assign(n_lines, 0.0);
@@ -1039,6 +1039,11 @@ nlte_status nlte_set_species(nlte_ctx *c, int n_lev, const double *E, const doub
     memcpy(dd + n_lev, g, sizeof(double) * n_lev);
     memcpy(dd + 2 * n_lev, T_K, sizeof(double) * n_T);
     if (n_coll) memcpy(dd + 2 * n_lev + n_T, K_ul, sizeof(double) * n_coll * n_T);
+    double *pairs = dd + 2 * n_lev + n_T + (size_t)n_coll * n_T;
+    for (int i = 0; i < n_coll; ++i) {
+        pairs[i] = E[c_up[i]] - E[c_lo[i]];
+        pairs[n_coll + i] = g[c_up[i]] / g[c_lo[i]];
+    }
     const size_t ibytes = ((sizeof(int32_t) * ni + 255) / 256) * 256;
     char *mem = nullptr;
     nlte_status st = dalloc(c, &mem, ibytes + sizeof(double) * nd);
@@ -1068,6 +1073,8 @@ nlte_status nlte_set_species(nlte_ctx *c, int n_lev, const double *E, const doub
     sp.g = sp.E + n_lev;
     sp.Ttab = sp.g + n_lev;
     sp.Ktab = sp.Ttab + n_T;
+    sp.cdE = sp.Ktab + (size_t)n_coll * n_T;
+    sp.cg = sp.cdE + n_coll;
     c->n_lev = n_lev;
     c->n_lines = n_lines;
     c->n_coll = n_coll;

@@ -41,6 +41,7 @@ struct SpeciesDev {
     const int32_t *lu, *ll, *cu, *cl;
     const double *A, *nu, *Bul, *Blu, *pre;  // pre = h nu / 4 pi
     const double *E, *g, *Ttab, *Ktab;
+    const double *cdE, *cg;   // [n_coll] E_u - E_l and g_u / g_l of the collision pairs
 };
 
 // Per-iteration convergence partials written by the stat-eq kernel.
