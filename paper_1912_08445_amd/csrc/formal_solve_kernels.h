@@ -24,8 +24,9 @@ namespace nlte {
 constexpr double kSqrt2 = 1.41421356237309504880;
 constexpr double kInv2Sqrt2 = 0.35355339059327376220;  // 1 / (2 sqrt 2)
 // The elimination state only grows (see elim_p); it is rescaled by a power of two once
-// any line's D passes 2^300, checked at least every fourth step, which leaves room for steps
-// with D_+ up to about 2^70 before the FP64 range ends.
+// any line's D passes 2^300, checked at least every fifth step.  A step multiplies D by at most
+// about D_+^2, so the FP64 range leaves room for steps with D_+ up to 2^70 (300 + 5 * 140 of
+// 1023).
 // Power-of-two rescaling is exact, so when it happens does not change any result.
 constexpr double kRenormAbove = 2.0370359763344861e90;   // 2^300
 
@@ -332,6 +333,15 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
     if (L == 0) return;
     T x_cur = 0, g_cur = 0, c[LPL];
     float travel = 0.0f;   // bounds how far x moved (any lane) since g was last evaluated exactly
+    int pend = 0;          // steps since rescaling was last checked
+    auto check = [&] {
+        rescale_if_big<LPL, TRACK>(ls);
+        pend = 0;
+    };
+    auto stepped = [&](int n) {
+        pend += n;
+        if (pend >= 4) check();
+    };
     for (int b0 = 0; b0 < L; b0 += ns - 1) {
         __syncthreads();
         // ---- stage nodes b0 .. b0+ns-1 in sweep order (far end first, O last)
@@ -417,7 +427,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                 // O's own offsets lie within the quadrature)
                 i += (int)__builtin_ctzll(~(far_mask >> i));
                 unrolled<LPL>([&](auto l) { elim_p<false>(0.0, (double)V.template src<l>(), ls.st[l]); });
-                rescale_if_big<LPL, TRACK>(ls);
+                stepped(1);
                 V = node.values(i);
                 x_cur = doppler<F32>(node.template own<0>(i, V), xq, node.template own<1>(i, V));
                 g_cur = profile(x_cur, tab);
@@ -456,7 +466,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                             c[l] = k2;
                         }
                     });
-                    rescale_if_big<LPL, TRACK>(ls);
+                    stepped(2);
                     g_cur = g2;
                     x_cur = x2;
                     V = V2;
@@ -517,12 +527,12 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                             const T G2 = profile(fma(t2, dx, x_cur), tab) * dzq;
                             sub_node(at(t1), G1);
                             sub_node(at(t2), G2);
-                            if (((j + 1) & 2) == 0) rescale_if_big<LPL, TRACK>(ls);   // (the end node checks too)
+                            stepped(2);
                         }
                     for (; j < m; ++j) {
                         const T t = (T)j;
                         sub_node(at(t), profile(fma(t, dx, x_cur), tab) * dzq);
-                        if ((j & 3) == 0) rescale_if_big<LPL, TRACK>(ls);
+                        stepped(1);
                     }
                 } else if constexpr (LONG && !F32) {
                     // x is linear in the sub-step index j, so g_j = e^{-x_j^2} obeys
@@ -543,6 +553,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                         travel = 0.0f;
                         budget = K;
                     }
+                    if (pend > 0) check();
                     int j = 0;
                     for (;;) {
                         const int jend = min(j + budget, m);
@@ -560,7 +571,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                             recur();
                             recur();
                             recur();
-                            rescale_if_big<LPL, TRACK>(ls);
+                            check();
                         }
                         // the last 0-3 steps in straight-line code
                         if (jint - k >= 2) {
@@ -568,6 +579,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                             recur();
                         }
                         if ((jint - k) & 1) recur();
+                        pend = jint - k;
                         travel += mdx * (float)(jint - j);
                         j = jint;
                         if (jend == m) {
@@ -576,6 +588,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                             travel += mdx;
                             break;
                         }
+                        if (pend > 0) check();
                         const double xj = fma((double)j, dx, x_cur);
                         Gj = exp_tab64(-(xj * xj), tab) * dzq;
                         r = exp_tab64(fmin(-(2.0 * xj + dx) * dx, 700.0), tab);
@@ -612,13 +625,12 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
                     }
                 });
             }
-            if (m > 1 || (i & 3) == 3) rescale_if_big<LPL, TRACK>(ls);
+            stepped(1);
             x_cur = xn;
             V = V1;
             if (kRows) V1 = Vn;
             if (TRACK) ls.m_last = m;
         }
-        rescale_if_big<LPL, TRACK>(ls);
     }
 }
 
