@@ -278,7 +278,8 @@ __device__ __forceinline__ bool far_segment(bool in, double a0, double b0, doubl
     const float lk = fmaxf(far.x, __shfl_down(far.x, 1)), lr = fmaxf(far.y, __shfl_down(far.y, 1));
     const float xm = (float)(fmin(fabs(b0), fabs(b1)) - fmax(a0, a1) * xq_max);
     const float x2 = xm * xm * 0.99999f;   // (rounded down: this is FP32)
-    const float tau2 = lk + lr + __builtin_amdgcn_logf((float)dz) - x2 * 1.44269504f;
+    // (dz < 2^its exponent; in FP32 a length under 1e-38 would be 0 and far whatever its opacity)
+    const float tau2 = lk + lr + (float)__builtin_amdgcn_frexp_exp(dz) - x2 * 1.44269504f;
     return in && b0 * b1 > 0.0 && xm > 0.0f && (tau2 < -66.0f || x2 > (F32 ? 105.0f : 750.0f));
 }
 
