@@ -10,7 +10,7 @@
 // At a node the photon of the sweep's own direction has comoving offset -y (y = a x - b
 // for the lane's x), the opposite one +y; with chi^- along the sweep direction cm,
 // chi_t = chi_line + chi_s, r = chi_s/chi_t and rm = cm/chi_t:
-//   S+ = S + r (Jbar - S) + rm dJ,   sigma~ = r dJ + rm Jbar   (Psi^-/chi_t, sweep direction),
+//   S+ = (chi_line/chi_t) S + r Jbar + rm dJ,   sigma~ = r dJ + rm Jbar   (Psi^-/chi_t, sweep direction),
 // Jbar = (Jw(-y) + Jw(y))/2, dJ = (Jw(-y) - Jw(y))/2.  The interior rows of the u-equation
 // gain -d sigma/dtau as the central difference over the two neighbours, those of the
 // v-equation -d S+/dtau; the boundary rows the half-node values.  Both equations share the
@@ -38,7 +38,7 @@
 // of +-y advances by a constant; the state is renormalised at every cell node and every
 // fourth sub-step (a check first, as in the line formal solve, measured no faster here).  With isotropic scattering two kinds of sub-step segment take shorter
 // forms: where every lane's lookups clamp, Jw is linear along the segment and the node values
-// come from the running Jbar - S and dJ; in the far wing (no line opacity beside the
+// come from the running Jbar and dJ; in the far wing (no line opacity beside the
 // scattering's) every node value
 // is linear in the sub-node index, so from the third sub-node on the differences across the
 // eliminated node are constants.  Besides J, L* (times chi_line/chi_t) and Jeff it returns Jw at the
@@ -176,10 +176,13 @@ struct NodeVal {
     double chit, Sp, sq;
 };
 
-// S+ = S + r (Jbar - S) + rm dJ and sigma~ = r dJ + rm Jbar with r = chi_s/chi_t, the
-// scattering share, and rm = cm/chi_t (safe for denormal far-wing opacities; cm = 0
-// wherever chi_s = 0).  Without scattering r = 0, so S+ is the line's S also where the line
-// opacity has underflowed to zero: the value does not jump where the profile underflows.
+// S+ = q S + r Jbar + rm dJ and sigma~ = r dJ + rm Jbar with q = chi_line/chi_t and
+// r = chi_s/chi_t, the shares of line and scattering, and rm = cm/chi_t (safe for denormal
+// far-wing opacities; cm = 0 wherever chi_s = 0).  Without scattering q = 1 and r = 0, so S+ is
+// the line's S also where the line opacity has underflowed to zero: the value does not jump
+// where the profile underflows.  (Both shares by themselves: S + r (Jbar - S) would carry the
+// rounding of r, 3e-15, times S, which beside strong scattering is far above the line's part
+// and, against a background in the Wien regime, above J.)
 template <bool ANISO>
 __device__ __forceinline__ NodeVal node_val(double cl, double cs, double cm, double S, double jp, double jm)
 {
@@ -190,8 +193,8 @@ __device__ __forceinline__ NodeVal node_val(double cl, double cs, double cm, dou
     double ic = __builtin_amdgcn_rcp(v.chit);
     ic = fma(ic, fma(-v.chit, ic, 1.0), ic);
     ic = cs > 0.0 ? ic : 0.0;   // chit >= cs > 0
-    const double r = cs * ic;
-    v.Sp = fma(0.5 * r, jp + jm, fma(-r, S, S));
+    const double r = cs * ic, q = fma(cl, ic, cs > 0.0 ? 0.0 : 1.0);
+    v.Sp = fma(0.5 * r, jp + jm, q * S);
     v.sq = (0.5 * kISq2 * r) * (jm - jp);
     if (ANISO) {
         const double rm = cm * ic;
@@ -201,18 +204,18 @@ __device__ __forceinline__ NodeVal node_val(double cl, double cs, double cm, dou
     return v;
 }
 
-// The same where Jw is linear along a segment (its lookups clamp), from the running
-// D = Jbar - S and Q = (Jw(-y) - Jw(y)) / (2 sqrt 2), themselves linear in the sub-node index:
-// S+ = S + r D, sigma~ / sqrt 2 = r Q (isotropic scattering).
-__device__ __forceinline__ NodeVal node_val_lin(double chit, double cs, double S, double D, double Q)
+// The same where Jw is linear along a segment (its lookups clamp), from the running Jb = Jbar
+// and Q = (Jw(-y) - Jw(y)) / (2 sqrt 2), themselves linear in the sub-node index:
+// S+ = q S + r Jb, sigma~ / sqrt 2 = r Q (isotropic scattering).
+__device__ __forceinline__ NodeVal node_val_lin(double cl, double cs, double S, double Jb, double Q)
 {
     NodeVal v;
-    v.chit = chit;
-    double ic = __builtin_amdgcn_rcp(chit);
-    ic = fma(ic, fma(-chit, ic, 1.0), ic);
+    v.chit = cl + cs;
+    double ic = __builtin_amdgcn_rcp(v.chit);
+    ic = fma(ic, fma(-v.chit, ic, 1.0), ic);
     ic = cs > 0.0 ? ic : 0.0;
-    const double r = cs * ic;
-    v.Sp = fma(r, D, S);
+    const double r = cs * ic, q = fma(cl, ic, cs > 0.0 ? 0.0 : 1.0);
+    v.Sp = fma(r, Jb, q * S);
     v.sq = r * Q;
     return v;
 }
@@ -295,13 +298,13 @@ __device__ __forceinline__ void step(HalfState &h, const NodeVal &v, double hz)
 // frame factor of the next sub-interval).
 struct SubRun {
     double g, r, kq, cs, cm, S, pos, tt, f;
-    double D, Q;   // clamped lookups, isotropic: node_val_lin's D and Q
+    double Jb, Q;   // clamped lookups, isotropic: node_val_lin's Jb and Q
 };
 
 // Jw end values of a segment whose lookups clamp: +y lookups a + t da, -y lookups a_m + t da_m.
 struct JEnds {
     double ap, dap, am, dam;
-    double dD, dQ;   // per sub-interval changes of node_val_lin's D and Q
+    double dJb, dQ;   // per sub-interval changes of node_val_lin's Jb and Q
 };
 
 template <bool UNI, bool ANISO, bool CLAMP, bool RENORM>
@@ -315,9 +318,9 @@ __device__ __forceinline__ void sub_step(HalfState &h, SubRun &w, double c, doub
     w.cs += dcs;
     w.S += dS;
     if constexpr (CLAMP && !ANISO) {
-        w.D += je.dD;
+        w.Jb += je.dJb;
         w.Q += je.dQ;
-        step<RENORM>(h, node_val_lin(fma(w.kq, w.g, w.cs), w.cs, w.S, w.D, w.Q), hz);
+        step<RENORM>(h, node_val_lin(w.kq * w.g, w.cs, w.S, w.Jb, w.Q), hz);
         return;
     }
     w.tt += im;
@@ -524,9 +527,9 @@ __device__ void half(const ScatArgs &a, const QGeo &qg, const double *tab, SNode
                     // (|y| > 27) cannot hide a profile above e^{-121}
                     const double u2 = 2.0 * dy * dy;
                     const double c = mdx <= 0.5 ? exp_neg_small(u2) : exp_le700(-u2);
-                    // (D and Q of node_val_lin at the segment's start and their changes)
-                    const double D0 = fma(0.5, ap + am, -S_cur), Q0 = (0.5 * kISq2) * (am - ap);
-                    const JEnds je{ap, dap, am, dam, fma(0.5 * im, dap + dam, -dS), (0.5 * kISq2 * im) * (dam - dap)};
+                    // (Jb and Q of node_val_lin at the segment's start and their changes)
+                    const double Jb0 = 0.5 * (ap + am), Q0 = (0.5 * kISq2) * (am - ap);
+                    const JEnds je{ap, dap, am, dam, (0.5 * im) * (dap + dam), (0.5 * kISq2 * im) * (dam - dap)};
                     SubRun w;
                     w.g = g_cur;
                     w.r = exp_tab64(fmin(-(2.0 * y_cur + dy) * dy, 700.0), tab);
@@ -537,7 +540,7 @@ __device__ void half(const ScatArgs &a, const QGeo &qg, const double *tab, SNode
                     w.pos = qpos<UNI>(qg, y_cur);
                     w.tt = 0.0;
                     w.f = f;
-                    w.D = D0;
+                    w.Jb = Jb0;
                     w.Q = Q0;
                     const double dpos = UNI ? dy * qg.inv_h : dy;
                     int budget = K;
@@ -583,7 +586,7 @@ __device__ void half(const ScatArgs &a, const QGeo &qg, const double *tab, SNode
                         w.cs = fma(fj, dcs, cs_cur);
                         w.S = fma(fj, dS, S_cur);
                         w.tt = fj * im;
-                        w.D = fma(fj, je.dD, D0);
+                        w.Jb = fma(fj, je.dJb, Jb0);
                         w.Q = fma(fj, je.dQ, Q0);
                         if (ANISO) {
                             w.cm = fma(fj, dcm, cm_cur);
