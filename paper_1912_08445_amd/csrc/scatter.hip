@@ -57,7 +57,7 @@ constexpr int kScatMaxQ = 256;
 constexpr int kChunk = 24;   // nodes staged per round
 constexpr double kSq2 = 1.41421356237309504880;
 constexpr double kISq2 = 0.70710678118654752440;
-
+constexpr int kNoBound = 1 << 20;   // SNode::sj where the ratio has no bound
 // Lookups in a J_nu row.  J(y) = row[i] + t (row[i+1] - row[i]) between the quadrature offsets i
 // and i + 1, constant beyond the outermost (one offset: constant everywhere).  The offsets are
 // symmetric, so -y sits in interval n_q - 2 - i at fraction 1 - t (the same value as its own
@@ -155,6 +155,7 @@ struct SNode {
     double Z, s, vw, a, b;
     double kap[2], S[2], cs[2], cm[2];   // cm: chi^- along the sweep direction
     const double *jrow[2];
+    int sj[2];                           // log2 of S over the smaller end value of the J_nu row, rounded up
 };
 
 // Segment from a staged node to the next: m sub-intervals of optical-depth weight
@@ -387,6 +388,10 @@ __device__ void half(const ScatArgs &a, const QGeo &qg, const double *tab, SNode
                     v.cm[l] = -((dp[0] * nx + dp[1] * ny) + dp[2] * nz);
                 }
                 v.jrow[l] = a.Jin + (c * a.n_lines + ln) * a.n_q;
+                const double j = fmin(v.jrow[l][0], v.jrow[l][a.n_q - 1]);
+                v.sj[l] = k.y == 0.0               ? -kNoBound
+                          : j > 0.0 && isfinite(k.y) ? __builtin_amdgcn_frexp_exp(k.y) - __builtin_amdgcn_frexp_exp(j) + 1
+                                                     : kNoBound;
             }
             nd[t] = v;
         }
@@ -416,15 +421,18 @@ __device__ void half(const ScatArgs &a, const QGeo &qg, const double *tab, SNode
                 e.dcs[l] = (q.cs[l] - p.cs[l]) * e.im;
                 e.dcm[l] = 0.0;
                 e.f0[l] = e.rho[l] = 1.0;
-                // chi_line < 2^-75 chi_s along the whole segment (both linear, the opacity at most
-                // e^{-y^2} times the larger end's) leaves chi, r and S+ (S up to 2^20 J) as they
-                // are without the line; 750: e^{-y^2} is 0.  (An outflow of 5,003 points, |y| > 8 in
-                // place of 27: 79% of the sub-steps, 59% before; 23.8 -> 22.9 ms with the points
-                // taken in decreasing cost.)
+                // chi_line < 2^-75 chi_s and chi_line S < 2^-55 chi_s J along the whole segment (all
+                // linear, the opacity at most e^{-y^2} times the larger end's, S and J at the ends
+                // of its rows, where far lookups clamp) leave chi, r and S+ as they are without the
+                // line: S enters where it passes 2^20 J (a background in the Wien regime).  750:
+                // e^{-y^2} is 0.  (An outflow of 5,003 points, |y| > 8 in place of 27: 79% of the
+                // sub-steps, 59% before; 23.8 -> 22.9 ms with the points taken in decreasing cost.)
                 const float kmax = (float)fmax(p.kap[l], q.kap[l]), cmin = (float)fmin(p.cs[l], q.cs[l]);
+                const int sj = max(p.sj[l], q.sj[l]);
                 e.y2_far[l] = 750.0f;
-                if (kmax < 1e30f && cmin > 1e-37f)
-                    e.y2_far[l] = fmaxf((__builtin_amdgcn_logf(fmaxf(kmax, 1e-37f)) - __builtin_amdgcn_logf(cmin) + 76.0f) * 0.6931472f, 1.0f);
+                if (kmax < 1e30f && cmin > 1e-37f && sj < kNoBound)
+                    e.y2_far[l] = fminf(fmaxf((__builtin_amdgcn_logf(fmaxf(kmax, 1e-37f)) - __builtin_amdgcn_logf(cmin) +
+                                               (float)(76 + max(sj - 20, 0))) * 0.6931472f, 1.0f), 750.0f);
                 if (ANISO) {
                     e.dcm[l] = (q.cm[l] - p.cm[l]) * e.im;
                     e.f0[l] = frame_exp(e.ds * fma(0.5, e.dcm[l], p.cm[l]));

@@ -45,3 +45,11 @@ def check(t_cmb, grid, dipole, dark):
 @pytest.mark.parametrize("dark", [False, True])
 def test_weak_background(t_cmb, grid, dipole, dark):
     check(t_cmb, grid, dipole, dark)
+
+
+@pytest.mark.parametrize("grid", ["uniform", "hermite"])
+@pytest.mark.parametrize("dipole", [False, True])
+def test_far_wings_light_dark_gas(grid, dipole):
+    """S / J from 2^79 to 2^318: the far wings, 2^-75 of the scattering opacity and less, are the
+    only light of the gas without line opacity."""
+    check(0.1, grid, dipole, False)
