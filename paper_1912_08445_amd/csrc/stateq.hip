@@ -130,7 +130,7 @@ __device__ __forceinline__ bool valid(int n, const double *x)
 // points, one point per lane.  The matrices are what bounds it: in private memory (256
 // doubles a lane, whatever the number of levels) their traffic to scratch took 0.55 ms for
 // 200,003 points of ten levels, two orders over the bytes of the call; N levels in registers,
-// assembled in N^2 * 512 bytes of LDS, take 0.15 ms (one pass of the call 586 -> 157 us; 91 with the
+// assembled in N^2 * 512 bytes of LDS, take 0.15 ms (one pass of the call 586 -> 157 us; 95 with the
 // shorter collision rates of rate_matrix), most of it the assembly: three waves fit a CU and
 // every transition updates four entries.  N stops at 11, whose
 // matrices fill 62 of the 64 KB a launch may ask for as it is; more levels stay with N = 0.
