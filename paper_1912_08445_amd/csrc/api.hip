@@ -41,6 +41,7 @@ nlte_status dalloc(nlte_ctx *c, T **p, size_t count)
     hipError_t e = hipMalloc((void **)p, sizeof(T) * count);
     if (e != hipSuccess) {
         *p = nullptr;
+        (void)hipGetLastError();   // (reported here, not by the next launch's check)
         return fail(c, NLTE_E_OOM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
     }
     return NLTE_OK;
@@ -572,7 +573,8 @@ nlte_status ensure_ng(nlte_ctx *c)
 // ------------------------------------------------------------------ band ALO helpers
 
 // Buffers of the band formal solve and the coupled solve for the current model, rays
-// and species, and the first cells of the walks.
+// and species, and the first cells of the walks.  band_dims names what they were sized for, and
+// nothing while they are replaced: a failed allocation leaves no key to a partial set.
 nlte_status ensure_band(nlte_ctx *c)
 {
     const int64_t P = c->P;
@@ -580,16 +582,13 @@ nlte_status ensure_band(nlte_ctx *c)
     const int64_t dims[5] = {P, n, nl, R, c->n_models};
     nlte_status st;
     if (memcmp(dims, c->band_dims, sizeof dims) != 0) {
+        memset(c->band_dims, 0, sizeof c->band_dims);
         if ((st = dalloc(c, &c->d_first, (size_t)P * R))) return st;
         if ((st = dalloc(c, &c->d_Jb, (size_t)P * nl))) return st;
         if ((st = dalloc(c, &c->d_Ld, (size_t)P * nl))) return st;
         if ((st = dalloc(c, &c->d_Ln, (size_t)P * nl * R))) return st;
         if ((st = dalloc(c, &c->d_bLU, (size_t)P * n * n))) return st;
         if ((st = dalloc(c, &c->d_bcpl, (size_t)P * nl * R))) return st;
-        // per-pair sums of a split band formal solve (at most the lines plus three idle slots)
-        const size_t pair_sums = (size_t)P * (nl + 3) * c->n_pairs * ((c->n_q + kWave - 1) / kWave) * 5;
-        c->bsum_count = pair_sums * sizeof(double) <= kPartBytes ? pair_sums : 0;
-        if (c->bsum_count > 0 && (st = dalloc(c, &c->d_bsum, c->bsum_count))) return st;
         if ((st = dalloc(c, &c->d_bperm, (size_t)P))) return st;
         if ((st = dalloc(c, &c->d_bvec, (size_t)P * n * 9))) return st;
         if ((st = dalloc(c, &c->d_bpart, (size_t)band_blocks(P) * 7))) return st;
@@ -600,6 +599,17 @@ nlte_status ensure_band(nlte_ctx *c)
         HIPCHK(c, hipHostMalloc((void **)&c->h_bstate, state, hipHostMallocDefault));
         memcpy(c->band_dims, dims, sizeof dims);
         c->first_valid = false;
+    }
+    // per-pair sums of a split band formal solve (at most the lines plus three idle slots),
+    // by the quadrature too
+    const size_t sums = (size_t)P * (nl + 3) * c->n_pairs * ((c->n_q + kWave - 1) / kWave) * 5;
+    if (sums * sizeof(double) > kPartBytes) {
+        dfree(c->d_bsum);
+        c->bsum_count = 0;
+    } else if (sums > c->bsum_count) {
+        c->bsum_count = 0;
+        if ((st = dalloc(c, &c->d_bsum, sums))) return st;
+        c->bsum_count = sums;
     }
     if (!c->first_valid) {
         HIPCHK(c, launch_first_cells(c->d_roff, c->d_rcells, P * R, c->d_first, c->stream));

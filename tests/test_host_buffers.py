@@ -1,0 +1,106 @@
+"""The library's host logic without a GPU, on a stand-in for the HIP runtime (fake_hip.c: host
+memory, launches that do nothing, allocations of one chosen size that fail): what is allocated
+when, and what is left of a context after an allocation failed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PREAMBLE = """
+import ctypes, sys
+sys.modules["torch"] = None              # the library is to bind to the stand-in, not to torch's runtime
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+fake.fake_fail_size.argtypes = fake.fake_count.argtypes = [ctypes.c_size_t]
+fake.fake_live.restype = ctypes.c_size_t
+sys.path[:0] = [sys.argv[2], sys.argv[2] + "/tests"]
+import numpy as np
+from paper_1912_08445_amd import binding
+from paper_1912_08445_amd.binding import NlteError, Solver
+from synth import configs, directions, species
+
+def setup(s, n, n_lev=2, nq=31, **params):
+    w = configs.sphere2(n_points=n, seed=1)
+    w.species = species.linear_rotor(n_lev)
+    w.quad_x, w.quad_w = directions.uniform_grid(nq, 4.0)
+    s.setup(w, **params)
+    return w
+
+def raises(code, f, *a):
+    try:
+        f(*a)
+    except NlteError as e:
+        assert e.code == code, (e.code, str(e))
+        return
+    raise AssertionError("no error")
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    if not os.path.exists(os.path.join(ROOT, "paper_1912_08445_amd", "libnlte.so")):
+        from paper_1912_08445_amd import build
+        build.build()
+    out = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", os.path.join(HERE, "fake_hip.c"), "-o", out],
+                   check=True)
+    return out
+
+
+def run(fake, body):
+    r = subprocess.run([sys.executable, "-c", PREAMBLE + body, fake, ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-2000:])
+
+
+def test_band_buffers_after_a_failed_growth(fake):
+    """Growing to a second model fails at the couplings; the first model then gets all of its
+    buffers anew, and the error does not stick to the next call's launches."""
+    run(fake, """
+s = Solver(0)
+w = setup(s, 100)
+pops = np.ones((100, 2))
+s.formal_solve_band(pops)
+setup(s, 200)
+for size in (200 * 12 * 8, 200 * 8, 200 * 2 * 9 * 8):     # couplings, row swaps, the solver's vectors
+    fake.fake_fail_size(size)
+    raises(binding.NLTE_E_OOM, s.formal_solve_band, np.ones((200, 2)))
+    fake.fake_fail_size(0)
+    setup(s, 100)
+    fake.fake_reset()
+    s.formal_solve_band(pops)
+    assert fake.fake_count(100 * 12 * 8) >= 2 and fake.fake_count(100 * 2 * 9 * 8) == 1, size
+    setup(s, 200)
+""")
+
+
+def test_band_pair_sums_follow_the_quadrature(fake):
+    """More offsets than a wave has lanes need more pair sums; too many for the limit give the
+    buffer back."""
+    run(fake, """
+s = Solver(0)
+n, pairs, lines = 2000, 6, 1
+def need(chunks):
+    return n * (lines + 3) * pairs * chunks * 5 * 8
+w = setup(s, n)
+pops = np.ones((n, 2))
+s.formal_solve_band(pops)
+assert fake.fake_count(need(1)) == 1
+fake.fake_reset()
+s.set_quadrature(*directions.uniform_grid(130, 4.0))
+s.formal_solve_band(pops)
+assert fake.fake_count(need(3)) == 1 and fake.fake_count(n * lines * 12 * 8) == 0
+s.set_quadrature(*directions.uniform_grid(31, 4.0))
+fake.fake_reset()
+s.formal_solve_band(pops)
+assert fake.fake_count(need(1)) == fake.fake_count(need(3)) == 0     # the larger one serves
+s.set_rays_healpix(9)
+s.trace()
+live = fake.fake_live()
+s.formal_solve_band(pops)
+R = 972
+assert n * (lines + 3) * (R // 2) * 5 * 8 > 64 << 20
+assert fake.fake_live() <= live - need(3) + (n * R * 4 + 2 * n * lines * R * 8) - (n * 12 * 4 + 2 * n * lines * 12 * 8)
+""")
