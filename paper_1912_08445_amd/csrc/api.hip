@@ -47,6 +47,27 @@ nlte_status dalloc(nlte_ctx *c, T **p, size_t count)
     return NLTE_OK;
 }
 
+// Make a buffer that only makes calls faster hold `count` entries: its capacity, 0 where memory
+// is short or count is 0 (the caller then does without).  A larger one is kept.
+template <typename T>
+void dalloc_optional(T *&p, size_t &capacity, size_t count)
+{
+    if (p && count > 0 && count <= capacity) return;
+    if (p) {
+        (void)hipDeviceSynchronize();   // as in dalloc
+        (void)hipFree(p);
+    }
+    p = nullptr;
+    capacity = 0;
+    if (count == 0) return;
+    if (hipMalloc((void **)&p, sizeof(T) * count) == hipSuccess) {
+        capacity = count;
+    } else {
+        p = nullptr;
+        (void)hipGetLastError();
+    }
+}
+
 template <typename T>
 void dfree(T *&p)
 {
@@ -603,14 +624,7 @@ nlte_status ensure_band(nlte_ctx *c)
     // per-pair sums of a split band formal solve (at most the lines plus three idle slots),
     // by the quadrature too
     const size_t sums = (size_t)P * (nl + 3) * c->n_pairs * ((c->n_q + kWave - 1) / kWave) * 5;
-    if (sums * sizeof(double) > kPartBytes) {
-        dfree(c->d_bsum);
-        c->bsum_count = 0;
-    } else if (sums > c->bsum_count) {
-        c->bsum_count = 0;
-        if ((st = dalloc(c, &c->d_bsum, sums))) return st;
-        c->bsum_count = sums;
-    }
+    dalloc_optional(c->d_bsum, c->bsum_count, sums * sizeof(double) <= kPartBytes ? sums : 0);
     if (!c->first_valid) {
         HIPCHK(c, launch_first_cells(c->d_roff, c->d_rcells, P * R, c->d_first, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1444,17 +1458,10 @@ nlte_status nlte_trace(nlte_ctx *c)
     auto t1 = std::chrono::steady_clock::now();
     c->st_trace.ms += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st_trace.launches += 1;
-    {   // room for the per-pair sums of split launches, where there are few enough points
-        const size_t need_bytes = sizeof(double) * (size_t)c->P * c->n_pairs * 3 * (c->n_lines + 2 * kMaxLpl) *
-                                  (c->n_q <= kWave ? 1 : (c->n_q + kWave - 1) / kWave);
-        if (need_bytes <= kPartBytes) {
-            if ((st = dalloc(c, (char **)&c->d_part, need_bytes))) return st;
-            c->part_bytes = need_bytes;
-        } else {
-            dfree(c->d_part);
-            c->part_bytes = 0;
-        }
-    }
+    // room for the per-pair sums of split launches, where there are few enough points
+    const size_t part_bytes = sizeof(double) * (size_t)c->P * c->n_pairs * 3 * (c->n_lines + 2 * kMaxLpl) *
+                              (c->n_q <= kWave ? 1 : (c->n_q + kWave - 1) / kWave);
+    dalloc_optional(c->d_part, c->part_bytes, part_bytes <= kPartBytes ? part_bytes : 0);
     c->total_cells = total;
     c->max_len = (int)h_sums[0];
     c->total_steps = (int64_t)h_sums[1] - n;

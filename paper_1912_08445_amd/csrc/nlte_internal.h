@@ -295,7 +295,7 @@ struct nlte_ctx {
     // work buffers (sized for P)
     void *d_lc = nullptr;  // line coefficients
     float2 *d_far = nullptr;  // [P] bounds of the far-wing test
-    void *d_part = nullptr;   // per-pair sums of split formal solves (sized by the trace)
+    char *d_part = nullptr;   // per-pair sums of split formal solves (sized by the trace; none: no split)
     size_t part_bytes = 0;
     double *d_pops_a = nullptr, *d_pops_b = nullptr;
     double *d_J = nullptr, *d_Jeff = nullptr, *d_L = nullptr;

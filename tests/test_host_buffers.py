@@ -104,3 +104,30 @@ R = 972
 assert n * (lines + 3) * (R // 2) * 5 * 8 > 64 << 20
 assert fake.fake_live() <= live - need(3) + (n * R * 4 + 2 * n * lines * R * 8) - (n * 12 * 4 + 2 * n * lines * 12 * 8)
 """)
+
+
+def test_trace_without_room_for_pair_sums(fake):
+    """The per-pair sums only make small models faster: a trace that has no room for them is a
+    trace all the same, and so is a band solve; a repeated trace keeps the buffer it has."""
+    run(fake, """
+s = Solver(0)
+n, pairs, lines = 300, 6, 1
+size, band = 8 * n * pairs * 3 * (lines + 10), n * (lines + 3) * pairs * 5 * 8
+fake.fake_fail_size(size)
+w = setup(s, n)
+pops = np.ones((n, 2))
+launches = fake.fake_launches()
+s.formal_solve(pops)
+unsplit = fake.fake_launches() - launches      # line coefficients and the sweep
+fake.fake_fail_size(band)
+s.formal_solve_band(pops)
+fake.fake_fail_size(0)
+s.trace()
+assert fake.fake_count(size) == 1
+launches = fake.fake_launches()
+s.formal_solve(pops)
+assert fake.fake_launches() - launches == unsplit + 1
+fake.fake_reset()
+s.trace()
+assert fake.fake_count(size) == 0
+""")
