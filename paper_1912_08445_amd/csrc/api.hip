@@ -1155,7 +1155,10 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
                 g[p * k + s] = (int32_t)(o + v);
             }
     }
-    // device copies
+    // device copies; without a model until all of it, the processing order and the work buffers
+    // included, is there
+    c->have_model = false;
+    c->traced = false;
     double *d_pos = nullptr, *d_vel = nullptr, *d_vt = nullptr, *d_X = nullptr;
     nlte_status st;
     if ((st = dalloc(c, &c->d_cell, P)) || (st = dalloc(c, &c->d_pn, P)) || (st = dalloc(c, &c->d_nh2, P)) || (st = dalloc(c, &c->d_T, P)) ||
@@ -1195,8 +1198,6 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
     c->k = k;
     c->n_models = n_models;
     c->offsets = off;
-    c->have_model = true;
-    c->traced = false;
     c->scat_on = false;     // scattering opacities belong to the previous points
     c->dip_on = false;
     c->jnu_last = -1;
@@ -1246,7 +1247,9 @@ nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, c
     HIPCHK(c, hipMemset(c->d_model_done, 0, n_models));
     HIPCHK(c, hipMemset(c->d_model_iters, 0, sizeof(int32_t) * n_models));
     HIPCHK(c, hipMemset(c->d_model_last, 0, sizeof(double) * n_models));
-    return ensure_work(c);
+    if ((st2 = ensure_work(c))) return st2;
+    c->have_model = true;
+    return NLTE_OK;
 }
 
 nlte_status nlte_set_rays(nlte_ctx *c, int n_rays, const double *dir)

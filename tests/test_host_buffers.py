@@ -131,3 +131,21 @@ fake.fake_reset()
 s.trace()
 assert fake.fake_count(size) == 0
 """)
+
+
+def test_no_model_after_a_failed_set_models(fake):
+    """The walk takes its points in the processing order that set_models leaves: a context whose
+    set_models failed anywhere has no model to trace."""
+    run(fake, """
+s = Solver(0)
+n = 300
+w = setup(s, n)
+for size in (4 * n, 4 * n * 12, 64 * n, 32 * n, 16 * n, 8 * n * 2):   # order, lists, records, staging, populations
+    fake.fake_fail_size(size)
+    raises(binding.NLTE_E_OOM, s.set_models, w.model)
+    fake.fake_fail_size(0)
+    raises(binding.NLTE_E_STATE, s.trace)
+    s.set_models(w.model)
+    s.trace()
+s.formal_solve(np.ones((n, 2)))
+""")
