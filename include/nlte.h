@@ -94,7 +94,8 @@ typedef struct {
                          for up to three lines per lane when the cached walks average more
                          than 3.5 elimination steps per cell, 2 in the FP32 form).  Either way
                          a run of segments beyond the line's range for every frequency is
-                         eliminated in one step.  The two agree to rounding.  -1 */
+                         eliminated in one step.  The two agree to rounding; the FP32 form with
+                         one, four or five lines per lane is one kernel, reported as short.  -1 */
     int stage_nodes;  /* ray nodes a formal-solve wave stages in LDS at a time, 2..64 (0 = by
                          rule: the most that keep the register budget's occupancy).  0 */
     int tile_points;  /* formal-solve work items (point, line block) a workgroup takes at a time,

@@ -183,8 +183,7 @@ nlte_status ensure_work(nlte_ctx *c)
     return NLTE_OK;
 }
 
-// Register budget (waves per SIMD), far-wing collapse, LDS staging depth and work
-// distribution of a formal-solve launch with a.lines_per_wave / a.ngrp lines per lane.
+// Register budget (waves per SIMD), segment mode, LDS staging depth and work distribution of a formal-solve launch with a.lines_per_wave / a.ngrp lines per lane.
 void set_launch_shape(nlte_ctx *c, SolveArgs &a, bool fp32)
 {
     const int lpl = a.lines_per_wave / a.ngrp;
@@ -199,9 +198,11 @@ void set_launch_shape(nlte_ctx *c, SolveArgs &a, bool fp32)
     // FP64 5.87 / 5.57 ms at 1.6, 5.87 / 5.46 at 3.1, 5.80 / 4.96 at 5.0, 6.15 / 4.43 at 13 (one line per lane: 3.94 /
     // 4.48 at 1.9, 4.34 / 4.21 at 3.8); FP32 3.89 / 4.03 at 1.6, 3.95 / 3.69 at 3.1.  Five lines
     // per lane: the recurrence's state spills in FP64 (10,011 points, nine lines: 4.25 / 6.67 at
-    // 1.9, 5.93 / 6.24 at 17), and in FP32 the modes are one kernel.
+    // 1.9, 5.93 / 6.24 at 17).
     const double per_cell = c->total_cells > 0 ? (double)c->total_steps / (double)c->total_cells : 0.0;
-    a.collapse = c->cfg.long_seg >= 0 ? c->cfg.long_seg : (lpl <= 3 && per_cell > (fp32 ? 2.0 : 3.5) ? 1 : 0);
+    a.long_mode = !fs_has_modes(fp32, lpl)  ? 0
+                  : c->cfg.long_seg >= 0 ? c->cfg.long_seg
+                                         : (lpl <= 3 && per_cell > (fp32 ? 2.0 : 3.5) ? 1 : 0);
     // the most staged nodes whose LDS keeps the register budget's occupancy (160 KiB per CU):
     // dynamic and static bytes in the units the hardware allocates (counted without them, the
     // disc's FP32 form took 48 nodes and lost one wave per CU to the rounding: 3.40 s per
@@ -1869,7 +1870,7 @@ nlte_status nlte_autotune(nlte_ctx *c, const char *cache_path, int trials, char 
         SolveConfig cur = saved;
         cur.lpl = a0.lines_per_wave / a0.ngrp;
         cur.waves = a0.waves;
-        cur.long_seg = a0.collapse;
+        cur.long_seg = a0.long_mode;
         cur.ns = a0.ns;
         cur.tile = a0.tile;
         auto restore = [&](nlte_status code) {
@@ -1886,8 +1887,10 @@ nlte_status nlte_autotune(nlte_ctx *c, const char *cache_path, int trials, char 
                 for (int v = 1; v <= lpl_cap; ++v) cand.push_back(v);
             else if (dim == 1)
                 cand = {1, 2, 3};
-            else if (dim == 2)
+            else if (dim == 2 && fs_has_modes(c->params.precision == NLTE_PREC_FP32_BULK, best.lpl))
                 cand = {0, 1};
+            else if (dim == 2)
+                best.long_seg = 0;   // one kernel
             else if (dim == 3)
                 cand = {16, 32, 48, 64};
             else if (dim == 4)
@@ -1955,7 +1958,7 @@ nlte_status nlte_get_launch(nlte_ctx *c, int *lines_per_lane, int *waves_per_sim
     const SolveArgs a = solve_args(c, nullptr, nullptr, nullptr);
     if (lines_per_lane) *lines_per_lane = a.lines_per_wave / a.ngrp;
     if (waves_per_simd) *waves_per_simd = a.waves;
-    if (long_segments) *long_segments = a.collapse;
+    if (long_segments) *long_segments = a.long_mode;
     if (stage_nodes) *stage_nodes = a.ns;
     if (persistent) *persistent = a.persistent;
     if (tile_points) *tile_points = a.tile;

@@ -925,19 +925,21 @@ hipError_t launch_fs_variant(const SolveArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <bool F32, int LPL, int W>
+hipError_t launch_fs_waves(const SolveArgs &a, hipStream_t s)
+{
+    if constexpr (fs_has_modes(F32, LPL)) {
+        if (a.long_mode) return launch_fs_variant<F32, LPL, W, true>(a, s);
+    }
+    return launch_fs_variant<F32, LPL, W, false>(a, s);
+}
+
 template <bool F32, int LPL>
 hipError_t launch_fs_lpl(const SolveArgs &a, hipStream_t s)
 {
-    // (in FP32 the modes differ in the pairs of segments only, see half_sweep)
-    const bool collapse = a.collapse && !(F32 && LPL >= 4);
-    if (a.waves == 3)
-        return collapse ? launch_fs_variant<F32, LPL, 3, true>(a, s)
-                          : launch_fs_variant<F32, LPL, 3, false>(a, s);
-    if (a.waves == 1)
-        return collapse ? launch_fs_variant<F32, LPL, 1, true>(a, s)
-                          : launch_fs_variant<F32, LPL, 1, false>(a, s);
-    return collapse ? launch_fs_variant<F32, LPL, 2, true>(a, s)
-                      : launch_fs_variant<F32, LPL, 2, false>(a, s);
+    if (a.waves == 3) return launch_fs_waves<F32, LPL, 3>(a, s);
+    if (a.waves == 1) return launch_fs_waves<F32, LPL, 1>(a, s);
+    return launch_fs_waves<F32, LPL, 2>(a, s);
 }
 
 template <bool F32>

@@ -21,9 +21,9 @@ size_t formal_solve_lds_f64(int lpl, int ns)
 }
 
 // Band-operator variant of the grid kernel: also the entries of the inverse system matrix
-// between O and its neighbour nodes (Jb, Ld, Ln of SolveArgs).  LONG: the long-segment
-// mode, profile recurrence and far-wing collapse (a collapsed last segment records a last
-// step of weight 0, as its zero-opacity sub-steps would).
+// between O and its neighbour nodes (Jb, Ld, Ln of SolveArgs), from the last step of each half
+// sweep (the segment that ends at O is never crossed as a far-wing one).  LONG: the long-segment
+// mode.
 template <int LPL, bool LONG>
 __global__ __launch_bounds__(64, 2) void k_formal_solve_band(SolveArgs a)
 {
@@ -53,11 +53,11 @@ hipError_t launch_formal_solve_band(const SolveArgs &a, hipStream_t s)
     const int lpl = a.lines_per_wave / a.ngrp;
     const int64_t nb8 = (a.n_blocks + 7) / 8;
     const dim3 grid((unsigned)(nb8 * 8));
-    if (lpl == 1 && a.collapse)
+    if (lpl == 1 && a.long_mode)
         hipLaunchKernelGGL((k_formal_solve_band<1, true>), grid, dim3(kWave), (fs_lds_bytes<false, 1>(a.ns)), s, a);
     else if (lpl == 1)
         hipLaunchKernelGGL((k_formal_solve_band<1, false>), grid, dim3(kWave), (fs_lds_bytes<false, 1>(a.ns)), s, a);
-    else if (lpl == 2 && a.collapse)
+    else if (lpl == 2 && a.long_mode)
         hipLaunchKernelGGL((k_formal_solve_band<2, true>), grid, dim3(kWave), (fs_lds_bytes<false, 2>(a.ns)), s, a);
     else if (lpl == 2)
         hipLaunchKernelGGL((k_formal_solve_band<2, false>), grid, dim3(kWave), (fs_lds_bytes<false, 2>(a.ns)), s, a);

@@ -82,7 +82,7 @@ struct SolveArgs {
     int fchunks;             // frequency chunks per wave (n_q > 64), else 1
     int ns;                  // ray nodes a wave stages in LDS per round (2..64)
     int waves;               // register budget of the launch: 2 or 3 waves per SIMD
-    int collapse;            // 1: long-segment mode (profile recurrence)
+    int long_mode;           // 1: long-segment mode (see fs_has_modes)
     int persistent;          // 1: workgroups take items in decreasing-cost order
     int tile;                // work items a workgroup takes at a time (1..16)
     int split;               // waves that share a point's ray pairs (1: none)
@@ -178,6 +178,10 @@ struct NgHist {
 
 // Launch choices of the formal solve (picked by rule or by the autotuner).
 constexpr int kMaxLpl = 5;    // lines per lane
+// Whether the long-segment mode is a kernel of its own: in FP64 it takes the profile by recurrence,
+// in FP32 it only leaves out the pairs of segments, which one line always has and four or five
+// never do.
+constexpr bool fs_has_modes(bool fp32, int lpl) { return !fp32 || lpl == 2 || lpl == 3; }
 struct SolveConfig {
     int lpl = 0;              // lines per lane (1..kMaxLpl; 0 = by rule)
     int waves = 0;            // register budget for 2 or 3 waves per SIMD (0 = by rule)

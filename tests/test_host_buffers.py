@@ -149,3 +149,18 @@ for size in (4 * n, 4 * n * 12, 64 * n, 32 * n, 16 * n, 8 * n * 2):   # order, l
     s.trace()
 s.formal_solve(np.ones((n, 2)))
 """)
+
+
+def test_reported_segment_mode_is_the_kernel_that_runs(fake):
+    """In FP32 the two segment modes are different kernels for two and three lines per lane only."""
+    run(fake, """
+s = Solver(0)
+w = setup(s, 50, n_lev=10)
+for precision in ("fp64", "fp32"):
+    for lpl in (1, 2, 3, 4, 5):
+        for mode in (0, 1):
+            s.set_params(precision=precision, lines_per_lane=lpl, long_segments=mode)
+            got = s.launch()
+            assert got["lines_per_lane"] == lpl
+            assert got["long_segments"] == (mode if precision == "fp64" or lpl in (2, 3) else 0), (precision, lpl, mode)
+""")
