@@ -71,7 +71,10 @@ struct Node {
     static constexpr int kStride = 4 * LPL + 6 + (ROWS ? 1 : 0);
 };
 
-// The value that lane N of this lane's row of 16 holds.
+// The value that lane N of this lane's row of 16 holds.  FP64 by one 64-bit move: the compiler's
+// builtin takes 32-bit values only, so its intrinsic is bound by name (a compiler without it stops
+// at an undefined symbol).  Two 32-bit moves in its place: the disc of 30,011 points 76.8 -> 79.4 ms,
+// the FP32 disc 44.8 -> 46.7, the outflow of 20,011 points 4.45 -> 4.60, its batched ALI 19.3 -> 20.2.
 extern "C" __device__ __attribute__((const)) long nlte_update_dpp_i64(long, long, int, int, int, bool)
     __asm("llvm.amdgcn.update.dpp.i64");
 template <int N>
