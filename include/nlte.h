@@ -266,10 +266,10 @@ nlte_status nlte_formal_solve_dev(nlte_ctx *ctx, const double *d_pops, double *d
  * serving loops, harnesses that forbid allocation): nlte_formal_solve_dev with the same
  * arguments, results and kernels, which allocates nothing.  Its scratch (the per-(point,
  * line) opacity and source staging, and two exponents per point for the far-wing test)
- * lives in fixed arrays of 64 MiB each in the library's device code, one of each per GPU,
+ * lives in a fixed array of 96 MiB (64 and 32) in the library's device code, one per GPU,
  * held until the process ends, instead of the context's buffers.  It takes P * n_lines
  * <= 4,194,288 in FP64 (8,388,576 in the FP32 form); larger models get NLTE_E_INVALID_ARG
- * (use nlte_formal_solve_dev).  Every call on one GPU shares that GPU's arrays, from any
+ * (use nlte_formal_solve_dev).  Every call on one GPU shares that GPU's array, from any
  * context: calls that overlap on one GPU (two streams, two threads) race and must be
  * ordered by the caller.  The call can be captured (kernels only, no memset node) and
  * never splits the pairs of few points.  No kernel timing or step counting (params.profile is ignored).

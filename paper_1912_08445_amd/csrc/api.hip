@@ -79,14 +79,13 @@ void dfree(T *&p)
 }
 
 // Scratch of the allocation-free formal solve (nlte_formal_solve_noalloc_dev): the
-// line-coefficient staging (after kScratchHead bytes) in the code object's global memory, one
+// line-coefficient staging and the far-wing exponents in the code object's global memory, one
 // copy per device, alive until the process ends.  Host code never names the array after
 // set-up: it uses the device address that hipGetSymbolAddress returned for that device.
-constexpr size_t kScratchBytes = size_t(64) << 20;
-constexpr size_t kScratchHead = 256;
-// The per-point bounds of the far-wing test follow the staging: 8 bytes per point, for as many
-// points as the staging can hold (FP32, one line).
-constexpr size_t kScratchFar = kScratchBytes;
+constexpr size_t kScratchBytes = (size_t(64) << 20) - 256;   // (the entry point's stated limit)
+// The exponents follow the staging: 4 bytes per point, for as many points as the staging can
+// hold (FP32, one line).
+constexpr size_t kScratchFar = kScratchBytes / sizeof(float2) * sizeof(short2);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchFar];
 
 constexpr int kMaxDevices = 64;
@@ -313,7 +312,7 @@ void drop_graphs(nlte_ctx *c)
 // timed, counted or allocated.
 struct FsScratch {
     void *lc;
-    float2 *far;
+    short2 *far;
 };
 
 nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, double *d_Jeff,
@@ -323,7 +322,7 @@ nlte_status formal_solve_impl(nlte_ctx *c, const double *d_pops, double *d_J, do
     const int fp32 = c->params.precision == NLTE_PREC_FP32_BULK;
     void *lcbuf = sc ? sc->lc : c->d_lc;
     int64_t *maser = ali ? c->d_maser : nullptr;   // inverted lines are reported by the ALI only
-    float2 *far = sc ? sc->far : c->d_far;
+    short2 *far = sc ? sc->far : c->d_far;
     auto lc = [&] { return launch_line_coef(c->sp, c->d_cell, d_pops, c->P, fp32, lcbuf, maser, c->d_ibdy, far, s); };
     HIPCHK(c, capture ? lc() : timed(c, c->st_line_coef, s, lc));
     SolveArgs a = solve_args(c, d_J, d_Jeff, d_L);
@@ -1581,16 +1580,16 @@ nlte_status nlte_formal_solve_noalloc_dev(nlte_ctx *c, const double *d_pops, dou
         return fail(c, NLTE_E_HIP, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(g_scratch_rc[c->device]));
     const size_t elem = c->params.precision == NLTE_PREC_FP32_BULK ? sizeof(float2) : sizeof(double2);
     const size_t need_bytes = (size_t)c->P * (size_t)c->n_lines * elem;
-    if (need_bytes > kScratchBytes - kScratchHead)
+    if (need_bytes > kScratchBytes)
         return fail(c, NLTE_E_INVALID_ARG,
                     "nlte_formal_solve_noalloc_dev: " + std::to_string(c->P) + " points x " +
                         std::to_string(c->n_lines) + " lines need " + std::to_string(need_bytes) +
                         " bytes of line-coefficient staging; the fixed scratch holds " +
-                        std::to_string(kScratchBytes - kScratchHead) + " (use nlte_formal_solve_dev)");
+                        std::to_string(kScratchBytes) + " (use nlte_formal_solve_dev)");
     (void)hipSetDevice(c->device);
     hipStream_t s = pick(c, stream);
     unsigned char *b8 = static_cast<unsigned char *>(base);
-    FsScratch sc{b8 + kScratchHead, reinterpret_cast<float2 *>(b8 + kScratchBytes)};
+    FsScratch sc{b8, reinterpret_cast<short2 *>(b8 + kScratchBytes)};
     // enqueue only: no event timing (which would synchronise), no step counting
     return formal_solve_impl(c, d_pops, d_J, d_Jeff, d_L, s, false, true, &sc);
 }

@@ -36,15 +36,15 @@ namespace nlte {
 // Non-positive opacity (population inversion) is clamped to kappa = S = 0 and counted.
 // One thread per (point, line), a block on whole points.  far (nullable): per point, powers of
 // two above the largest kappa and the largest S / I_bdy (at least 1) of its lines, as
-// exponents: the formal solve's far-wing test reads these 8 bytes per cell instead of every
+// exponents: the formal solve's far-wing test reads these 4 bytes per cell instead of every
 // line's coefficients.
 template <bool F32>
 __global__ __launch_bounds__(256) void k_line_coef(SpeciesDev sp, const CellRec *__restrict__ cell,
                                                    const double *__restrict__ pops, int64_t P,
                                                    void *__restrict__ lc, unsigned long long *__restrict__ maser,
-                                                   const double *__restrict__ ibdy, float2 *__restrict__ far)
+                                                   const double *__restrict__ ibdy, short2 *__restrict__ far)
 {
-    __shared__ float2 s_far[256];
+    __shared__ short2 s_far[256];
     const int nl = sp.n_lines, per_block = 256 / nl;
     const int lp = threadIdx.x / nl, l = threadIdx.x - lp * nl;
     const int64_t p = blockIdx.x * (int64_t)per_block + lp;
@@ -69,29 +69,29 @@ __global__ __launch_bounds__(256) void k_line_coef(SpeciesDev sp, const CellRec 
         else
             reinterpret_cast<double2 *>(lc)[p * nl + l] = make_double2(kap, S);
         if (far) {
-            // (NaN or infinite values compare false or exceed every bound in far_segment)
+            // (without a bound: 32767, above every opacity that far_segment takes for none)
             const double I = ibdy[l];
             const int eI = I > 0.0 ? __builtin_amdgcn_frexp_exp(I) : -1000000;
-            const float ek = kap == 0.0 ? -3000.0f : (isfinite(kap) ? (float)__builtin_amdgcn_frexp_exp(kap) : 1e9f);
-            const float es = S == 0.0 ? 0.0f : (isfinite(S) ? (float)(__builtin_amdgcn_frexp_exp(S) - eI + 1) : 1e9f);
-            s_far[threadIdx.x] = make_float2(ek, fmaxf(es, 0.0f));
+            const int ek = kap == 0.0 ? -3000 : (isfinite(kap) ? __builtin_amdgcn_frexp_exp(kap) : 32767);
+            const int es = S == 0.0 ? 0 : (isfinite(S) ? __builtin_amdgcn_frexp_exp(S) - eI + 1 : 32767);
+            s_far[threadIdx.x] = make_short2((short)ek, (short)min(max(es, 0), 32767));
         }
     }
     if (!far) return;
     __syncthreads();
     if (on && l == 0) {
-        float2 f = s_far[threadIdx.x];
+        short2 f = s_far[threadIdx.x];
         for (int i = 1; i < nl; ++i) {
-            const float2 v = s_far[threadIdx.x + i];
-            f.x = fmaxf(f.x, v.x);
-            f.y = fmaxf(f.y, v.y);
+            const short2 v = s_far[threadIdx.x + i];
+            f.x = max(f.x, v.x);
+            f.y = max(f.y, v.y);
         }
         far[p] = f;
     }
 }
 
 hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops, int64_t P, int fp32,
-                            void *lc, int64_t *maser_count, const double *ibdy, float2 *far, hipStream_t s)
+                            void *lc, int64_t *maser_count, const double *ibdy, short2 *far, hipStream_t s)
 {
     if (P * sp.n_lines == 0) return hipSuccess;
     const int per_block = 256 / sp.n_lines;

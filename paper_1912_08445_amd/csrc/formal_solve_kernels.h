@@ -276,13 +276,14 @@ __device__ __forceinline__ void rescale_if_big(LineState<LPL> &ls)
 // The test costs the staging lanes about 20 instructions per round, none per segment.)
 template <bool F32>
 __device__ __forceinline__ bool far_segment(bool in, double a0, double b0, double a1, double b1, double dz,
-                                            double xq_max, float2 far)
+                                            double xq_max, short2 far)
 {
-    const float lk = fmaxf(far.x, __shfl_down(far.x, 1)), lr = fmaxf(far.y, __shfl_down(far.y, 1));
+    const short2 next = __builtin_bit_cast(short2, __shfl_down(__builtin_bit_cast(int, far), 1));
+    const float lkr = (float)(max((int)far.x, (int)next.x) + max((int)far.y, (int)next.y));
     const float xm = (float)(fmin(fabs(b0), fabs(b1)) - fmax(a0, a1) * xq_max);
     const float x2 = xm * xm * 0.99999f;   // (rounded down: this is FP32)
     // (dz < 2^its exponent; in FP32 a length under 1e-38 would be 0 and far whatever its opacity)
-    const float tau2 = lk + lr + (float)__builtin_amdgcn_frexp_exp(dz) - x2 * 1.44269504f;
+    const float tau2 = lkr + (float)__builtin_amdgcn_frexp_exp(dz) - x2 * 1.44269504f;
     return in && b0 * b1 > 0.0 && xm > 0.0f && (tau2 < -66.0f || x2 > (F32 ? 105.0f : 750.0f));
 }
 
@@ -374,7 +375,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
         const bool seg = s < L && lane < ns - 1;   // this lane's node starts a segment of the round
         // segments of this round that every frequency crosses beyond the line's range
         const unsigned long long far_mask = __ballot(
-            far_segment<F32>(seg, an, bn, an1, bn1, Zs - Zn, a.xq_max, load ? a.far[cidx] : float2{0.f, 0.f}));
+            far_segment<F32>(seg, an, bn, an1, bn1, Zs - Zn, a.xq_max, load ? a.far[cidx] : short2{0, 0}));
         int m_seg = 1, K_seg = 64;   // sub-intervals, and the restart interval of the recurrence (0: direct)
         float dx_seg = 0.0f;         // bound on |dx| over every frequency
         if (load) {

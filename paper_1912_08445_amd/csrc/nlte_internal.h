@@ -63,7 +63,7 @@ struct ConvResult {
 struct SolveArgs {
     const CellRec *cell;
     const void *lc;          // [P][n_lines] (kappa, S): double2 (FP64) or float2 (FP32 bulk)
-    const float2 *far;       // [P] log2 of the largest kappa and S / I_bdy of a cell's lines (see k_line_coef)
+    const short2 *far;       // [P] log2 of the largest kappa and S / I_bdy of a cell's lines (see k_line_coef)
     const int64_t *roff;     // [P * n_rays + 1]
     const int32_t *rcells;   // cached walks, global point indices, nearest first
     const double *dir;       // [n_rays][3]
@@ -298,7 +298,7 @@ struct nlte_ctx {
 
     // work buffers (sized for P)
     void *d_lc = nullptr;  // line coefficients
-    float2 *d_far = nullptr;  // [P] bounds of the far-wing test
+    short2 *d_far = nullptr;  // [P] bounds of the far-wing test
     char *d_part = nullptr;   // per-pair sums of split formal solves (sized by the trace; none: no split)
     size_t part_bytes = 0;
     double *d_pops_a = nullptr, *d_pops_b = nullptr;
@@ -413,7 +413,7 @@ hipError_t launch_trace_sums(const int64_t *len, int64_t n, const unsigned long 
 hipError_t scan_lengths(int64_t *len_then_off, int64_t n, void *tmp, size_t *tmp_bytes,
                         hipStream_t s);
 hipError_t launch_line_coef(const SpeciesDev &sp, const CellRec *cell, const double *pops,
-                            int64_t P, int fp32, void *lc, int64_t *maser_count, const double *ibdy, float2 *far,
+                            int64_t P, int fp32, void *lc, int64_t *maser_count, const double *ibdy, short2 *far,
                             hipStream_t s);
 hipError_t launch_formal_solve(const SolveArgs &a, int fp32, hipStream_t s);
 hipError_t launch_formal_solve_f64(const SolveArgs &a, hipStream_t s);

@@ -8,12 +8,14 @@
 #include <string.h>
 
 static size_t fail_size, live_bytes, sizes[1 << 16];
+static size_t largest_var;
 static int n_sizes, n_launches;
 static hipError_t last = hipSuccess;
 
 void fake_fail_size(size_t n) { fail_size = n; }
 void fake_reset(void) { n_sizes = n_launches = 0; }
 size_t fake_live(void) { return live_bytes; }
+size_t fake_largest_var(void) { return largest_var; }
 int fake_launches(void) { return n_launches; }
 int fake_count(size_t n)
 {
@@ -122,5 +124,6 @@ void __hipRegisterFunction(void **m, const void *h, char *d, const char *n, unsi
 }
 void __hipRegisterVar(void **m, void *v, char *h, char *d, int e, size_t n, int c, int g)
 {
-    (void)m, (void)v, (void)h, (void)d, (void)e, (void)n, (void)c, (void)g;
+    (void)m, (void)v, (void)h, (void)d, (void)e, (void)c, (void)g;
+    if (n > largest_var) largest_var = n;
 }

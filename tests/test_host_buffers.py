@@ -164,3 +164,19 @@ for precision in ("fp64", "fp32"):
             assert got["lines_per_lane"] == lpl
             assert got["long_segments"] == (mode if precision == "fp64" or lpl in (2, 3) else 0), (precision, lpl, mode)
 """)
+
+
+def test_memory_of_the_far_wing_exponents(fake):
+    """Four bytes a point: beside the 64 MiB of staging that the allocation-free solve's fixed array
+    holds, half as much for the most points it takes."""
+    run(fake, """
+s = Solver(0)
+fake.fake_largest_var.restype = ctypes.c_size_t
+assert 64 << 20 < fake.fake_largest_var() <= 96 << 20
+n = 777
+w = configs.sphere2(n_points=n, seed=1)
+s.set_species(w.species)
+before = fake.fake_count(4 * n)
+s.set_models(w.model)
+assert fake.fake_count(4 * n) - before >= 1
+""")
