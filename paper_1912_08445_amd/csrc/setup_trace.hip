@@ -85,16 +85,19 @@ hipError_t launch_lte(const SpeciesDev &sp, const CellRec *cell, const double *T
 // n the direction, p = e + d - (d.n) n is off by less than 5e-7 (|e| + |d|) and q = |p|^2 by
 // less than 2.4e-6 (e^2 + d^2); the FP64 values themselves are off by about 1e-15 R, less
 // than 1e-7 |d| since cells with a neighbour nearer than 1e-8 R take the FP64 step.  Two
-// values of q differ by more than 1e-5 (e^2 + max d^2), or the step is repeated; so is one
-// where some |d.n| <= 2e-6 |d|, whose sign FP32 may miss (lattices with axis rays, rare
-// otherwise).
+// values of q differ by more than 1e-5 (e^2 + max d^2), or the step is repeated.  A neighbour
+// with |d.n| <= 2e-6 |d|, whose sign FP32 may miss, is never taken without the repeat, but asks
+// for it only where its q rivals the best candidate's.  Across an axis ray of a lattice it does
+// not: the walks of two axis rays through 30^3 points took 0.50 ms with a repeat wherever there
+// is such a neighbour, 0.34 now, 0.43 in FP64 alone; 60^3 points 2.87, 1.13 and 4.02.
 //
 // A workgroup takes 64 points next to each other in Morton order and one direction, so that
 // its walks cross the same cells and have similar lengths; an XCD takes a contiguous range
 // of such groups, all directions of the same points after one another.
 //
-// Measured on the outflow of 50,000 points with 48 rays (84 M steps): count 2.63 ms with the
-// step counts, fill 2.36 ms.  One lane per ray, one point's rays per wave and 32-byte FP64
+// Measured on the outflow of 50,000 points with 48 rays (84 M steps): count 2.31 ms with the
+// step counts, fill 1.83 ms (2.63 and 2.36 with branches on candidates and rivals in place of
+// selects).  One lane per ray, one point's rays per wave and 32-byte FP64
 // slots took 10.4 and 11.0 ms, and the step counts 1.6 ms more in a kernel of their own.
 
 __device__ __forceinline__ float quad_xor1(float v)
@@ -175,7 +178,6 @@ __global__ __launch_bounds__(256) void k_walk(WalkArgs a, int64_t *__restrict__ 
             const NbrSlot *slots = a.tab + cur * kp;
             float bq = INFINITY, q2 = INFINITY, dmax = 0.0f;
             int32_t best = -1;
-            int amb = 0;
 #pragma unroll 3
             for (int s = sub; s < kp; s += 4) {
                 const NbrSlot e = slots[s];
@@ -183,15 +185,14 @@ __global__ __launch_bounds__(256) void k_walk(WalkArgs a, int64_t *__restrict__ 
                 const float px = ex + fmaf(-dn, fx, e.x), py = ey + fmaf(-dn, fy, e.y), pz = ez + fmaf(-dn, fz, e.z);
                 const float qq = fmaf(pz, pz, fmaf(py, py, px * px));
                 const float d2 = fmaf(e.z, e.z, fmaf(e.y, e.y, e.x * e.x));
-                if (e.m >= 0 && !(dn * dn > 4e-12f * d2)) amb = 1;   // (NaN: a cell that needs FP64)
-                if (e.m >= 0 && dn > 0.0f) {
-                    dmax = fmaxf(dmax, d2);
-                    q2 = fminf(q2, fmaxf(bq, qq));
-                    if (qq < bq) {
-                        bq = qq;
-                        best = e.m;
-                    }
-                }
+                // ahead for certain: a candidate; ahead or not: a rival (NaN: a cell that needs FP64)
+                const bool sure = dn * dn > 4e-12f * d2;
+                const float qc = e.m >= 0 && sure && dn > 0.0f ? qq : INFINITY;
+                const float qr = e.m >= 0 && !sure ? (qq >= 0.0f ? qq : -1.0f) : INFINITY;
+                dmax = fmaxf(dmax, d2);
+                q2 = fminf(fminf(q2, qr), fmaxf(bq, qc));
+                best = qc < bq ? e.m : best;
+                bq = fminf(bq, qc);
             }
             {
                 float oq = quad_xor1(bq);
@@ -206,11 +207,9 @@ __global__ __launch_bounds__(256) void k_walk(WalkArgs a, int64_t *__restrict__ 
                 bq = fminf(bq, oq);
                 dmax = fmaxf(dmax, quad_xor1(dmax));
                 dmax = fmaxf(dmax, quad_xor2(dmax));
-                amb |= quad_xor1(amb);
-                amb |= quad_xor2(amb);
             }
-            if (q2 < INFINITY && !(q2 - bq > 1e-5f * (fmaf(ez, ez, fmaf(ey, ey, ex * ex)) + dmax))) amb = 1;
-            if (amb) best = exact_step(a.cell, slots, kp, sub, ox, oy, oz, nx, ny, nz, zcur);
+            if (q2 < INFINITY && !(q2 - bq > 1e-5f * (fmaf(ez, ez, fmaf(ey, ey, ex * ex)) + dmax)))
+                best = exact_step(a.cell, slots, kp, sub, ox, oy, oz, nx, ny, nz, zcur);
             if (best < 0) break;
             if (FILL) {
                 if ((int)(len & 3) == sub) hold = best;
