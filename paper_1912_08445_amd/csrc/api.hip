@@ -230,11 +230,11 @@ size_t part_need(const SolveArgs &a, bool fp32)
 // Waves that share a point's ray pairs: where the points alone would fill the chip's wave
 // slots fewer than eight times, the pairs are split to make up that many work items (at most
 // one pair each).  Below one filling a wave's chain of dependent loads and steps sets the time,
-// up to a few the last, partly filled round does.  Measured, one iteration without / with:
-// sphere of 1,000 points (0.3 fillings) 65 / 42 us; outflows of 600 (0.2) 705 / 206 us, 3,000
-// (1.0) 1058 / 748, 10,000 (3.3) 667 / 632; discs of 1,000 (0.5) 5.70 / 3.21 ms, 5,000 (2.4)
-// 3.98 / 3.81, 10,000 with six pairs (4.9) 1.87 / 1.90; more items than that cost as much as
-// they bring (16 fillings: outflows 658 and 762 us of 632 and 748).
+// up to a few the last, partly filled round does.  The formal solve without / with a split, 30
+// calls in a row: sphere of 1,000 points and six pairs (0.3 fillings) 57 / 38 us; outflows of 600
+// points and 24 pairs (0.2) 815 / 207 us, 3,000 (1.0) 883 / 692, of 10,000 and six pairs (3.3)
+// 592 / 579; discs of 1,000 and 96 pairs (0.5) 5.31 / 2.85 ms, 5,000 and 24 (2.4) 3.22 / 3.13,
+// 10,000 and six (4.9) 1.56 / 1.58; twice as many items cost as much as they bring.
 int64_t split_items(const nlte_ctx *c, const SolveArgs &a) { return (int64_t)c->n_cu * 4 * a.waves * 8; }
 
 void set_split(nlte_ctx *c, SolveArgs &a, bool fp32)

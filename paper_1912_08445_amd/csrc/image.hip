@@ -21,9 +21,10 @@
 // exact restarts after at most 16 widths of travel; cell nodes and short segments
 // evaluate the exponential directly.  The state only grows; it is rescaled by a power of two
 // once d passes 2^300, checked at least every fourth step.
-// Instruction issue bounds it (5,000 vector instructions per wave, issued 99% of the time): 64
-// channels of a disc of 40,009 points took 340 us with an exponential of degree 11 and a
-// rescaling at every node, now 300.
+// Instruction issue bounds it (5,000 vector instructions per wave, issued 99% of the time), so its
+// time follows the clock: 64 channels of a disc of 40,009 points 301 us in a long series, 435
+// within ten calls of an idle GPU; with an exponential of degree 11 and a rescaling at every
+// node 353 and 505.
 #include "nlte_internal.h"
 #include "device_math.h"
 
@@ -44,7 +45,7 @@ struct alignas(16) ImgNode {
 
 // Up to this many sub-steps the profile is evaluated directly: the recurrence takes two
 // exponentials to start and saves one per inner sub-node and the end node's (the disc's
-// image at 1, 2, 3, 5, 8: 486, 395, 389, 397, 403 us in one series, 447 before).
+// image at 1, 2, 3, 5, 8: 486, 395, 389, 397, 403 us in one short series).
 constexpr int kDirect = 3;
 
 constexpr double kRescaleAbove = 2.0370359763344861e90;   // 2^300
