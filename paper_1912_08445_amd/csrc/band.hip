@@ -21,8 +21,9 @@
 // product forms its operand from the old vectors where it reads it.
 // Launches and their latency bound it for few points: with a synchronisation for each set of
 // inner products and vector updates as kernels of their own, an iteration of the band ALO for a
-// sphere of 3,001 points (4 steps) took 610 us, now 250, of which the formal solve takes 98 (143
-// before its pairs were split over waves).
+// sphere of 3,001 points (4 steps) took 590 us, now 215, of which the formal solve takes 85 (132
+// before its pairs were split over waves).  The solver's kernels keep 0.15 waves on a SIMD and
+// read 0.3 TB/s: a chain of waits (the scalars' partial sums, then the couplings, then the factors).
 #include <algorithm>
 
 #include "rates.h"
