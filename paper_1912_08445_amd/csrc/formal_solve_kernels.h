@@ -345,7 +345,7 @@ __device__ __forceinline__ void half_sweep(const SolveArgs &a, typename Bulk<F32
     };
     auto stepped = [&](int n) {
         pend += n;
-        if (pend >= 4) check();
+        if (pend >= (LPL >= 4 ? 5 : 4)) check();   // (steps come singly, or at most two at a time)
     };
     for (int b0 = 0; b0 < L; b0 += ns - 1) {
         __syncthreads();
