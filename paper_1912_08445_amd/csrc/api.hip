@@ -157,9 +157,16 @@ nlte_status upload_ibdy(nlte_ctx *c)
         double nu = c->nu[l];
         ib[l] = 2.0 * kH * nu * nu * nu / (kC * kC) / expm1(kH * nu / (kKB * c->params.t_cmb));
     }
-    nlte_status st = dalloc(c, &c->d_ibdy, c->n_lines);
+    double *fresh = nullptr;   // (what is there stays until this is complete)
+    nlte_status st = dalloc(c, &fresh, c->n_lines);
     if (st) return st;
-    HIPCHK(c, hipMemcpy(c->d_ibdy, ib.data(), sizeof(double) * c->n_lines, hipMemcpyHostToDevice));
+    const hipError_t e = hipMemcpy(fresh, ib.data(), sizeof(double) * c->n_lines, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        dfree(fresh);
+        return fail(c, NLTE_E_HIP, std::string("boundary intensities: ") + hipGetErrorString(e));
+    }
+    dfree(c->d_ibdy);
+    c->d_ibdy = fresh;
     return NLTE_OK;
 }
 
@@ -430,6 +437,7 @@ nlte_status mlp_alloc(nlte_ctx *c, int n_out)
 {
     if (n_out < 1 || n_out > kMaxLev) return fail(c, NLTE_E_INVALID_ARG, "n_out must be in 1..16");
     MlpState &m = c->mlp;
+    m.ready = false;
     m.dims = mlp_dims(n_out);
     const int64_t np = m.dims.n_params;
     nlte_status st;
@@ -468,6 +476,7 @@ nlte_status mlp_ensure_batch(nlte_ctx *c, int batch)
 {
     MlpState &m = c->mlp;
     if (batch <= m.batch_cap) return NLTE_OK;
+    m.batch_cap = 0;   // (here and below: a capacity says nothing while its buffers are replaced)
     nlte_status st;
     if ((st = dalloc(c, &m.d_gpart, (size_t)mlp_train_chunks(batch) * m.dims.n_params))) return st;
     if ((st = dalloc(c, &m.d_lpart, (size_t)mlp_train_ld(batch) / 16))) return st;
@@ -481,6 +490,7 @@ nlte_status mlp_ensure_rows(nlte_ctx *c, int64_t rows)
 {
     MlpState &m = c->mlp;
     if (rows <= m.rows_cap) return NLTE_OK;
+    m.rows_cap = 0;
     nlte_status st;
     if ((st = dalloc(c, &m.d_x, (size_t)rows * 8))) return st;
     if ((st = dalloc(c, &m.d_y, (size_t)rows * 16))) return st;
@@ -492,6 +502,7 @@ nlte_status mlp_ensure_points(nlte_ctx *c)
 {
     MlpState &m = c->mlp;
     if (c->P <= m.pred_cap) return NLTE_OK;
+    m.pred_cap = 0;
     nlte_status st;
     if ((st = dalloc(c, &m.d_feat, (size_t)c->P * 8))) return st;
     if ((st = dalloc(c, &m.d_xp, (size_t)c->P * 8))) return st;
@@ -577,10 +588,12 @@ nlte_status ensure_ng(nlte_ctx *c)
     const int64_t need = (int64_t)M * c->P * c->n_lev;
     nlte_status st;
     if (need > c->ng_hist_elems) {
+        c->ng_hist_elems = 0;
         if ((st = dalloc(c, &c->d_ng_hist, (size_t)need))) return st;
         c->ng_hist_elems = need;
     }
-    if (c->n_models > c->ng_models_cap || !c->d_ng_rej) {
+    if (c->n_models > c->ng_models_cap) {
+        c->ng_models_cap = 0;
         const int K = kNgMaxM - 2;
         if ((st = dalloc(c, &c->d_ng_part, (size_t)c->n_models * ng_chunks() * (K * (K + 1) / 2 + K)))) return st;
         if ((st = dalloc(c, &c->d_ng_coef, (size_t)c->n_models * (kNgMaxM - 1)))) return st;
@@ -820,7 +833,9 @@ nlte_status formal_solve_scat_impl(nlte_ctx *c, const double *d_pops, const doub
 nlte_status ensure_jnu(nlte_ctx *c)
 {
     const int64_t n = c->P * c->n_lines * c->n_q;
-    if (n != c->jnu_elems || !c->d_jnu[0]) {
+    if (n != c->jnu_elems) {
+        c->jnu_elems = 0;
+        c->jnu_last = -1;
         nlte_status st;
         if ((st = dalloc(c, &c->d_jnu[0], (size_t)n)) || (st = dalloc(c, &c->d_jnu[1], (size_t)n))) return st;
         c->jnu_elems = n;
@@ -1068,6 +1083,7 @@ nlte_status nlte_set_species(nlte_ctx *c, int n_lev, const double *E, const doub
         pairs[i] = E[c_up[i]] - E[c_lo[i]];
         pairs[n_coll + i] = g[c_up[i]] / g[c_lo[i]];
     }
+    c->have_species = false;   // until all of it is there
     const size_t ibytes = ((sizeof(int32_t) * ni + 255) / 256) * 256;
     char *mem = nullptr;
     nlte_status st = dalloc(c, &mem, ibytes + sizeof(double) * nd);
@@ -1112,7 +1128,9 @@ nlte_status nlte_set_species(nlte_ctx *c, int n_lev, const double *E, const doub
     // line widths and work buffers depend on the species: the model must be set again
     c->have_model = false;
     c->traced = false;
-    return upload_ibdy(c);
+    st = upload_ibdy(c);
+    if (st) c->have_species = false;
+    return st;
 }
 
 nlte_status nlte_set_models(nlte_ctx *c, int n_models, const int64_t *offsets, const double *pos,
@@ -1274,6 +1292,8 @@ nlte_status nlte_set_rays(nlte_ctx *c, int n_rays, const double *dir)
     }
     for (int r = 0; r < n_rays; ++r)
         if (r < anti[r]) pr.push_back(r);
+    c->have_rays = false;
+    c->traced = false;
     nlte_status st;
     if ((st = dalloc(c, &c->d_dir, 3 * (size_t)n_rays)) || (st = dalloc(c, &c->d_anti, n_rays)) ||
         (st = dalloc(c, &c->d_pair_r, pr.size())))
@@ -1347,6 +1367,7 @@ nlte_status nlte_set_quadrature(nlte_ctx *c, int n_q, const double *x, const dou
         sw += w[n];
     }
     if (fabs(sw - 1.0) > 1e-12) return fail(c, NLTE_E_INVALID_ARG, "quadrature weights must sum to 1");
+    c->have_quad = false;
     nlte_status st;
     if ((st = dalloc(c, &c->d_qx, n_q)) || (st = dalloc(c, &c->d_qw, n_q))) return st;
     HIPCHK(c, hipMemcpy(c->d_qx, x, sizeof(double) * n_q, hipMemcpyHostToDevice));
@@ -1389,7 +1410,13 @@ nlte_status nlte_set_params(nlte_ctx *c, const nlte_params *p)
                     "parameter out of range (lines_per_lane: 0..5; waves_per_simd: 0..3; long_segments: -1..1; "
                     "stage_nodes: 0 or 2..64; tile_points: 0..16; ng_every: 0 or 3..8; "
                     "alo_band: 0, or 1 with use_alo)");
+    const nlte_params keep = c->params;
     c->params = *p;
+    const nlte_status st = upload_ibdy(c);
+    if (st) {
+        c->params = keep;
+        return st;
+    }
     c->cfg.lpl = p->lines_per_lane;
     c->cfg.waves = p->waves_per_simd;
     c->cfg.long_seg = p->long_segments;
@@ -1397,7 +1424,7 @@ nlte_status nlte_set_params(nlte_ctx *c, const nlte_params *p)
     c->cfg.tile = p->tile_points;
     c->cfg.persistent = p->persistent ? 1 : 0;
     drop_graphs(c);
-    return upload_ibdy(c);
+    return NLTE_OK;
 }
 
 nlte_status nlte_trace(nlte_ctx *c)
@@ -2142,8 +2169,10 @@ nlte_status nlte_mlp_loss_grad(nlte_ctx *c, const float *X, const float *T, int6
     const int no = m.dims.out[3];
     if ((st = mlp_ensure_rows(c, n))) return st;
     if ((st = mlp_ensure_batch(c, (int)n))) return st;
-    if (!m.d_loss && (st = dalloc(c, &m.d_loss, 1))) return st;
-    if (m.loss_cap < 1) m.loss_cap = 1;
+    if (m.loss_cap < 1) {
+        if ((st = dalloc(c, &m.d_loss, 1))) return st;
+        m.loss_cap = 1;
+    }
     HIPCHK(c, hipMemcpyAsync(m.d_x, X, sizeof(float) * n * 8, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(m.d_y, T, sizeof(float) * n * no, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, launch_mlp_train(m.d_frags, m.d_theta, m.dims, m.d_x, m.d_y, n, 0, (int)n, m.d_ht, m.d_dzt,
@@ -2184,6 +2213,7 @@ nlte_status nlte_mlp_train(nlte_ctx *c, const float *X, const float *T, int64_t 
     const int no = m.dims.out[3];
     if ((st = mlp_ensure_rows(c, n))) return st;
     if (tp->steps > m.loss_cap) {
+        m.loss_cap = 0;
         if ((st = dalloc(c, &m.d_loss, (size_t)tp->steps))) return st;
         m.loss_cap = tp->steps;
     }
@@ -2458,6 +2488,7 @@ nlte_status nlte_image_dev(nlte_ctx *c, const double *d_pops, int ray, int line,
     HIPCHK(c, hipSetDevice(c->device));
     hipStream_t s = pick(c, stream);
     if (n_ch > c->vch_cap) {
+        c->vch_cap = 0;
         if ((st = dalloc(c, &c->d_vch, (size_t)n_ch))) return st;
         c->vch_cap = n_ch;
     }

@@ -180,3 +180,65 @@ before = fake.fake_count(4 * n)
 s.set_models(w.model)
 assert fake.fake_count(4 * n) - before >= 1
 """)
+
+
+def test_failed_growth_leaves_no_stale_capacity(fake):
+    """Buffers that grow on demand: a failed growth leaves nothing that a smaller call takes for
+    its own."""
+    run(fake, """
+s = Solver(0)
+n = 300
+w = setup(s, n)
+pops = np.ones((n, 2))
+v = np.linspace(-1e5, 1e5, 70)
+
+def grows(size, call, fails, again):
+    call()
+    fake.fake_fail_size(size)
+    raises(binding.NLTE_E_OOM, fails)
+    fake.fake_fail_size(0)
+    fake.fake_reset()
+    call()                              # (a missing buffer would end the process here)
+    assert fake.fake_count(again) >= 1, size
+
+x, g = np.zeros((900, 8), np.float32), np.zeros((900, 2), np.float32)
+grows(70 * 8, lambda: s.image(pops, 0, 0, v[:64]), lambda: s.image(pops, 0, 0, v), 64 * 8)
+s.mlp_init(2)
+grows(900 * 8 * 4, lambda: s.mlp_forward(x[:100]), lambda: s.mlp_forward(x), 100 * 8 * 4)
+grows(900 * 16 * 4, lambda: s.mlp_forward(x[:100]), lambda: s.mlp_forward(x), 100 * 16 * 4)
+grows(77 * 4, lambda: s.mlp_train(x[:50], g[:50], steps=3, batch=50), lambda: s.mlp_train(x[:50], g[:50], steps=77, batch=50), 3 * 4)
+chi = np.ones((n, 1)) * 1e-16
+s.set_scattering(chi)
+jnu = np.ones((n, 1, 31))
+call = lambda: s.formal_solve_scat(pops, jnu)
+def other():
+    s.set_quadrature(*directions.uniform_grid(47, 4.0))
+    s.formal_solve_scat(pops, np.ones((n, 1, 47)))
+def back():
+    s.set_quadrature(*directions.uniform_grid(31, 4.0))
+    call()
+grows(n * 47 * 8, back, other, n * 31 * 8)
+
+# what a call replaces is gone, or kept, but never half there
+q = directions.uniform_grid(15, 4.0)
+fake.fake_fail_size(15 * 8)
+raises(binding.NLTE_E_OOM, s.set_quadrature, *q)
+raises(binding.NLTE_E_STATE, s.formal_solve, pops)
+fake.fake_fail_size(0)
+s.set_quadrature(*q)
+fake.fake_fail_size(8)                  # the boundary intensity of one line
+t_cmb = s.params.t_cmb
+raises(binding.NLTE_E_OOM, lambda: s.set_params(t_cmb=5.0))
+fake.fake_fail_size(0)
+s.set_params(t_cmb=t_cmb)
+s.formal_solve(pops)
+fake.fake_fail_size(48 * 3 * 8)
+raises(binding.NLTE_E_OOM, s.set_rays_healpix, 2)
+raises(binding.NLTE_E_STATE, s.trace)
+fake.fake_fail_size(0)
+s.set_rays_healpix(2)
+s.trace()
+fake.fake_fail_size(4 * 8)
+raises(binding.NLTE_E_OOM, s.set_species, species.linear_rotor(5))
+raises(binding.NLTE_E_STATE, s.set_models, w.model)
+""")
